@@ -33,7 +33,8 @@ BYTES_PER_SITE = {"fp32_dev": 216, "fp64": 432}
 STORED_BYTES_PER_SITE = {"fp32_dev": 224, "fp64": 432}
 REPEATS = 5
 # the step kernel and its launch shape and store policy (host_layout.h)
-KERNEL_SOURCES = ("paper_1412_6238_amd/csrc/step_kernel.h", "paper_1412_6238_amd/csrc/lattice.h",
+KERNEL_SOURCES = ("paper_1412_6238_amd/csrc/step_kernel.h", "paper_1412_6238_amd/csrc/pair_kernel.h",
+                  "paper_1412_6238_amd/csrc/lattice.h",
                   "paper_1412_6238_amd/csrc/host_layout.h")
 
 

@@ -68,6 +68,18 @@ struct AdjArgs {
   int ntx;             // tiles along x
 };
 
+// constants in the kernel's arithmetic type
+template <typename R>
+struct Consts {
+  R rho, inv_rho, rcv, tauf0, dtauf, tauT0, dtauT, wg, gam3, kcap, epsalpha;
+  R sigma0, sigmaT, bfx, bfy;
+  __device__ explicit Consts(const StepArgs &a)
+      : rho(R(a.rho)), inv_rho(R(1.0 / a.rho)), rcv(R(a.rcv)), tauf0(R(a.tauf0)),
+        dtauf(R(a.dtauf)), tauT0(R(a.tauT0)), dtauT(R(a.dtauT)), wg(R(a.omg_g)),
+        gam3(R(a.gam3)), kcap(R(a.kcap)), epsalpha(R(a.epsalpha)), sigma0(R(a.sigma0)),
+        sigmaT(R(a.sigmaT)), bfx(R(a.rho * a.ax)), bfy(R(a.rho * a.ay)) {}
+};
+
 // ---- transpose of one site's collision -------------------------------------
 // Inputs: the site's moments (p, j, T or their deviations; c in FP64), its
 // stencil values, lam (cotangents of the 27 post-collision values of the site)

@@ -239,6 +239,63 @@ inline Launch pick_launch(int nx, int ny, bool fp32, bool two_ahead) {
 // two fluid densities (rho2 > 0 and different from rho)
 inline bool two_densities(const lbe_csf_params *p) { return p->rho2 > 0.0 && p->rho2 != p->rho; }
 
+// Two plain steps per launch (pair_step_kernel): strips of columns and chunks
+// of rows, one wave each; rows = 0 where the steps go one by one.
+//
+// Taken where a state no longer fits the caches, or close to it: FP32 from
+// 1.1M sites, FP64 from half a million (one density).  Measured on MI355X
+// against one launch per step, interleaved windows, us per step, FP32: 4096^2
+// 735 -> 417, 4096 x 1024 181 -> 118, 1500^2 116 -> 77, 1200^2 80 -> 52, and
+// below the line 1024^2 36.3 -> 36.9, 1030 x 777 28.4 -> 32.8, 512 x 1024
+// 19.9 -> 27.8; FP64: 4096^2 1385 -> 720, 2048^2 360 -> 195, 1030 x 777
+// 80 -> 51, 800^2 62 -> 40, 512 x 1024 37 -> 33, below it 600^2 27.3 -> 26.6.
+// (The chunks of a small grid are short against the eight rows that their
+// cones add.)
+//
+// A block's waves take neighbouring strips and march in step, so that the
+// lines at their seams are read and written by one CU at one time: on 4096^2
+// eight FP32 waves a block took 406 us, four 463, two 471, one 557; four FP64
+// waves 702, two 729, one 893 (HBM bytes 1.5 times the state with one).  On
+// smaller grids that fit blocks less evenly fewer waves are as fast or
+// faster: 1200^2 FP32 53.2 with one against 55.4 with eight, FP64 82.3 with
+// two against 86.0 with four.  One block more than are resident at once would
+// run alone, so the chunks are as many as fit (FP32 eight waves a CU, FP64
+// four, by registers and LDS).
+constexpr int kPairHalo = 4;                    // columns on each side that only feed the others
+constexpr int kPairCols = 64 - 2 * kPairHalo;   // columns a wave owns
+constexpr size_t kPairMaxBytes = 0xffff0000u;   // state size below the dropped stores' offset
+struct PairLaunch {
+  int nw, nstrips, rows, nblocks;   // waves a block, strips (one wave each), rows a chunk, blocks
+  int nparts;                       // waves with sites: diagnostic partials
+};
+inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
+  PairLaunch L{0, 0, 0, 0, 0};
+  const bool fp32 = p->precision == LBE_CSF_FP32_DEV;
+  const char *e = std::getenv("LBE_CSF_PAIR");
+  const bool forced = e && std::atoi(e) == 1;
+  if (two_densities(p) || p->ny < 8 || state_bytes > kPairMaxBytes) return L;
+  if (e && !forced) return L;
+  // the overrides of the one-step kernels ask for those kernels
+  for (const char *v : {"LBE_CSF_NW", "LBE_CSF_ROWS", "LBE_CSF_PIPE", "LBE_CSF_STREAM",
+                        "LBE_CSF_TILE", "LBE_CSF_SMALL"})
+    if (!forced && std::getenv(v)) return L;
+  const size_t n = (size_t)p->nx * p->ny;
+  if (!forced && n < (size_t)(fp32 ? 1100000 : 500000)) return L;
+  L.nw = n > 3000000 ? (fp32 ? 8 : 4) : (fp32 ? 1 : 2);
+  const int ngroups = ((p->nx + kPairCols - 1) / kPairCols + L.nw - 1) / L.nw;
+  const int slots = kNumCUs * (fp32 ? 8 : 4) / L.nw;
+  // strips fill their blocks evenly; a grid with few columns takes fewer
+  const int wx = std::max(4, (p->nx + ngroups * L.nw - 1) / (ngroups * L.nw));
+  L.nstrips = (p->nx + wx - 1) / wx;
+  const int chunks = std::max(1, slots / ngroups);
+  L.rows = (p->ny + chunks - 1) / chunks;
+  if (const char *r = std::getenv("LBE_CSF_PAIR_ROWS")) L.rows = std::max(1, std::min(p->ny, std::atoi(r)));
+  const int nchunks = (p->ny + L.rows - 1) / L.rows;
+  L.nblocks = ngroups * nchunks;
+  L.nparts = L.nstrips * nchunks;
+  return L;
+}
+
 struct Layout {
   size_t state_bytes;
   size_t off_a, off_b, off_tw, off_part, off_ring, off_cnt, off_rec, off_pc, off_adj, total;
@@ -295,8 +352,10 @@ inline Layout make_layout(const lbe_csf_params *p, int64_t record_steps) {
   L.off_a = o; o = align_up(o + L.state_bytes);
   L.off_b = o; o = align_up(o + L.state_bytes);
   L.off_tw = o; o = align_up(o + 2 * (size_t)p->nx * 8);
-  // diagnostic partials: one per block of the row-marching or the tile kernel
-  const size_t nparts = (size_t)std::max(la.nblocks, tile_blocks(p->nx, p->ny));
+  // diagnostic partials: one per block of the row-marching or the tile kernel,
+  // or per wave of the two-step kernel
+  const size_t nparts = (size_t)std::max({la.nblocks, tile_blocks(p->nx, p->ny),
+                                          pair_launch(p, L.state_bytes).nparts});
   L.off_part = o; o = align_up(o + nparts * kNumPartials * 8);
   L.off_ring = o; o = align_up(o + (size_t)kDiagRing * sizeof(DiagRecord));
   L.off_cnt = o; o = align_up(o + 4 * sizeof(int64_t));

@@ -36,6 +36,21 @@ enum : int {
                 // that write whole lines bypass that cache (buf_store_stream)
 };
 
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+
+// Constants of a site's collision in the arithmetic type: formed on the host
+// in FP64 and rounded once, so that no lane divides or converts them.
+template <typename R>
+struct SiteConsts {
+  R omg, chg;         // 1 / tau_g and (tau_g - 1/2) 3 / rho
+  R omT, chT;         // the same of tau_T where it is constant
+  R tauT0, dtauT;     // tau_T(c) = tauT0 + clamp(c) dtauT
+  R rho, rcv, i3rho;  // rho, rho cv, 3 / rho
+  R shift;            // rho cv Tg / 36 (FP32 form): change of reference of a
+                      // diagonal population that moves up one row
+};
+
 // Everything a step launch needs, passed by value.  Derived constants are
 // computed once on the host in FP64 and rounded to the kernel's arithmetic
 // type inside the kernel.
@@ -47,6 +62,12 @@ struct StepArgs {
   const double *twb, *twt;  // wall temperatures [nx]
   // physical and derived constants
   double rho, cv, rcv;      // rho, cv, rho*cv
+  double inv_rho, inv_rcv, rho3;   // 1/rho, 1/(rho cv), rho/3
+  double omf, chf;          // 1/tau_f and tau_f - 1/2 where tau_f is constant
+  double epsT;              // eps alpha sigmaT, with the sign of the Marangoni term
+  SiteConsts<float> kf;
+  SiteConsts<double> kd;
+  int vartau;               // tau_f or tau_T varies with c
   double tauf0, dtauf;      // tau_f(c) = tauf0 + clamp(c) dtauf
   double tauT0, dtauT;
   double omg_g;             // 1 / tau_g
@@ -70,6 +91,12 @@ struct StepArgs {
   // FP32 form), each a plane of nx*ny
   void *tape;
 };
+
+template <typename R>
+__device__ __forceinline__ const SiteConsts<R> &site_consts(const StepArgs &a) {
+  if constexpr (sizeof(R) == 8) return a.kd;
+  else return a.kf;
+}
 
 // Buffer resources: one descriptor per buffer (scalar registers) and a 32-bit
 // byte offset per lane, so a load or store needs one vector register for its

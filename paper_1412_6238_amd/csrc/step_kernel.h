@@ -122,18 +122,6 @@ __device__ __forceinline__ void rest_set(void *state, size_t nx, size_t y, size_
                         rest_base<S>(W, nx))[x] = T(v);
 }
 
-// constants in the kernel's arithmetic type
-template <typename R>
-struct Consts {
-  R rho, inv_rho, rcv, tauf0, dtauf, tauT0, dtauT, wg, gam3, kcap, epsalpha;
-  R sigma0, sigmaT, bfx, bfy;
-  __device__ explicit Consts(const StepArgs &a)
-      : rho(R(a.rho)), inv_rho(R(1.0 / a.rho)), rcv(R(a.rcv)), tauf0(R(a.tauf0)),
-        dtauf(R(a.dtauf)), tauT0(R(a.tauT0)), dtauT(R(a.dtauT)), wg(R(a.omg_g)),
-        gam3(R(a.gam3)), kcap(R(a.kcap)), epsalpha(R(a.epsalpha)), sigma0(R(a.sigma0)),
-        sigmaT(R(a.sigmaT)), bfx(R(a.rho * a.ax)), bfy(R(a.rho * a.ay)) {}
-};
-
 // One row of a lane's column: v[q] for the 25 storage planes (v[9], v[18]
 // unused) and the two rest populations as stored.
 template <typename R>
@@ -185,306 +173,406 @@ __device__ __forceinline__ void site_moments(const RowVals<R> &r, double inv_rcv
   *p = f;
 }
 
-// The collision, diagnostics and field output of site (x, j).  cS/cC/cN,
+// One pair of opposite directions (i, o) of one lattice: with xi = xi_i,
+// b = 3 xi.u, Q = b^2/2 - 3/2 u^2 and a force vector X already times
+// (tau - 1/2), equilibrium and forcing of the pair are w (E + O) and
+// w (E - O),
+//   E = K0 + K1 Q + b X1.xi,   O = K1 b + X0.xi + Q X1.xi
+// (X1 differs from X0 only by the density terms of Eq. 6), and a population
+// relaxes as v - om (v - w (E +- O)): one difference of nearby values and
+// one fused multiply-add each.
+template <typename R>
+struct PairEq {
+  R E, O;
+};
+template <typename R>
+__device__ __forceinline__ PairEq<R> pair_eq(R b, R Q, R K0, R K1, R X0, R X1) {
+  return {fma_(Q, K1, fma_(b, X1, K0)), fma_(b, K1, fma_(X1, Q, X0))};
+}
+template <typename R>
+__device__ __forceinline__ R relax(R v, R w, R eq, R om) {
+  return fma_(-om, fma_(-w, eq, v), v);
+}
+
+// Moments, stencils, closures and collision of site (x, j), with its
+// diagnostics and field output.  With kStore the post-collision values go to
+// sink(i, lattice, value) as they are formed, so that their stores spread over
+// the collision, and the two rest populations to sink.rest(g0, h0).  The
+// directions come pair by pair, or with BYDIR in their order 1, 2, 3, ...,
+// which holds two pairs at a time: the row-marching FP32 step on 4096^2 stores
+// 2.5% faster that way (737 against 756 us), the two-step kernel has no
+// registers for it (470 against 406 us).  A value of hbar already holds the
+// deviation against the reference of the row it moves to and, in a direction
+// that a wall reflects, the wall term of the anti-bounce-back.  cS/cC/cN,
 // tS.., pS.. point at the ring entries west of the site in rows j-1, j, j+1
-// (index 0 west, 1 centre, 2 east).
-// With LDSOUT the post-collision values go to a state in LDS (lds_dst) in
-// the plane-major layout of lds_plane_off instead of to a.dst.
-template <typename S, typename R, bool DEV, int MODE, bool LDSOUT = false>
-__device__ __forceinline__ void site_update(const StepArgs &a, const Consts<R> &k, int j, int x,
-                                            const double *cS, const double *cC, const double *cN,
-                                            const R *tS, const R *tC, const R *tN, const R *pS,
-                                            const R *pC, const R *pN, const RowVals<R> &cur,
-                                            double *acc, char *lds_dst = nullptr) {
+// (index 0 west, 1 centre, 2 east).  bot and top: the row touches that wall
+// (never without WALL).
+//
+// What bounds it: vector instructions (one wave64 FP32 or FP64 operation
+// takes four cycles of a SIMD), and on small grids their dependent chain.  So
+// opposite directions share their even and odd parts (pair_eq: 11 operations
+// and 3 a population, for each of the three lattices), the Marangoni term
+// eps alpha (|grad c|^2 grad s - (grad c.grad s) grad c) is written as the
+// equal eps alpha (gcy, -gcx) (gcy gsx - gcx gsy), and constants derived from
+// the parameters come from the host (StepArgs).  Multiply-adds are fused
+// where written and nowhere else, so that every kernel that inlines this
+// gives the same bits.
+template <typename R, bool DEV, int MODE, bool WALL, bool BYDIR, typename Sink>
+__device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bool bot, bool top,
+                                             const double *cS, const double *cC, const double *cN,
+                                             const R *tS, const R *tC, const R *tN, const R *pS,
+                                             const R *pC, const R *pN, const RowVals<R> &cur,
+                                             double *acc, Sink &&sink) {
+#pragma clang fp contract(off)
   constexpr bool VR = (MODE & kVarRho) != 0;
-  const int nx = a.nx, ny = a.ny;
-  const size_t n = (size_t)nx * (size_t)ny;
+  const SiteConsts<R> &k = site_consts<R>(a);
+  const size_t n = (size_t)a.nx * (size_t)a.ny;
   // order parameter and its stencils in FP64
   const double cd = cC[1];
-  double gcx_d, gcy_d, lap_d, mu_d, tHt = 0.0;
+  double gcx, gcy, mu, tHt = 0.0;
   {
     const double e = cC[2], w = cC[0], nn = cN[1], s = cS[1];
     const double ne = cN[2], nw = cN[0], sw = cS[0], se = cS[2];
-    gcx_d = (e - w) * (1.0 / 3.0) + (ne + se - nw - sw) * (1.0 / 12.0);
-    gcy_d = (nn - s) * (1.0 / 3.0) + (ne + nw - se - sw) * (1.0 / 12.0);
+    const double d1 = ne - sw, d2 = se - nw;
+    gcx = fma_(e - w, 1.0 / 3.0, (d1 + d2) * (1.0 / 12.0));
+    gcy = fma_(nn - s, 1.0 / 3.0, (d1 - d2) * (1.0 / 12.0));
     const double dx2 = (e - cd) + (w - cd), dy2 = (nn - cd) + (s - cd);
     const double dd = (ne - cd) + (nw - cd) + (se - cd) + (sw - cd);
-    lap_d = (2.0 / 3.0) * (dx2 + dy2) + (1.0 / 6.0) * dd;
-    mu_d = a.beta2 * cd * (cd - 1.0) * (2.0 * cd - 1.0) - a.eps2 * lap_d;
+    const double lap = fma_(dx2 + dy2, 2.0 / 3.0, dd * (1.0 / 6.0));
+    mu = fma_(a.beta2 * (cd * (cd - 1.0)), fma_(2.0, cd, -1.0), -a.eps2 * lap);
     if (MODE & kCurv) {
       // Hessian of c on the same nine points (exact on quadratics) and the
       // second derivative along the unit tangent t = (-gy, gx)/|grad c|,
       // which equals |grad c| div n for n = grad c/|grad c|
-      const double hxx = (2.0 / 3.0) * dx2 - (1.0 / 3.0) * dy2 + (1.0 / 6.0) * dd;
-      const double hyy = (2.0 / 3.0) * dy2 - (1.0 / 3.0) * dx2 + (1.0 / 6.0) * dd;
+      const double hxx = fma_(2.0 / 3.0, dx2, fma_(-1.0 / 3.0, dy2, dd * (1.0 / 6.0)));
+      const double hyy = fma_(2.0 / 3.0, dy2, fma_(-1.0 / 3.0, dx2, dd * (1.0 / 6.0)));
       const double hxy = 0.25 * ((ne - nw) - (se - sw));
-      const double gg = gcx_d * gcx_d + gcy_d * gcy_d;
+      const double gg = fma_(gcx, gcx, gcy * gcy);
       if (gg > 0.0)
-        tHt = (gcy_d * gcy_d * hxx - 2.0 * gcx_d * gcy_d * hxy + gcx_d * gcx_d * hyy) / gg;
+        tHt = fma_(gcy * gcy, hxx, fma_(-2.0 * gcx * gcy, hxy, gcx * gcx * hyy)) / gg;
     }
   }
-  const R c = R(cd);
   const R Tv = tC[1];   // T, or Delta T = T - Trow in the FP32 form
   const R pv = pC[1];   // p, or Delta p
   // FP32 form: temperatures are stored relative to the linear reference
   // Ts + Tg y; Trow is its value at this row's centre
-  const double Trow = DEV ? a.Ts + a.Tg * (double(j) + 0.5) : 0.0;
+  const double Trow = DEV ? fma_(a.Tg, double(j) + 0.5, a.Ts) : 0.0;
   // Stencils of T and p, the force and the velocity are evaluated in FP64.
   // Near an interface they are small differences of larger terms (the
   // capillary force against the pressure gradient in Fbar = F - grad p, the
   // momentum against the half force in u), so in the FP32 form the
   // arithmetic, not the storage, would otherwise set the error.
-  auto grad = [&](const R *Sr, const R *Cr, const R *Nr, double *gx, double *gy) {
-    *gx = (double(Cr[2]) - double(Cr[0])) * (1.0 / 3.0) +
-          (double(Nr[2]) + double(Sr[2]) - double(Nr[0]) - double(Sr[0])) * (1.0 / 12.0);
-    *gy = (double(Nr[1]) - double(Sr[1])) * (1.0 / 3.0) +
-          (double(Nr[2]) + double(Nr[0]) - double(Sr[2]) - double(Sr[0])) * (1.0 / 12.0);
+  auto grad = [](const R *Sr, const R *Cr, const R *Nr, double *gx, double *gy) {
+#pragma clang fp contract(off)
+    const double d1 = double(Nr[2]) - double(Sr[0]), d2 = double(Sr[2]) - double(Nr[0]);
+    *gx = fma_(double(Cr[2]) - double(Cr[0]), 1.0 / 3.0, (d1 + d2) * (1.0 / 12.0));
+    *gy = fma_(double(Nr[1]) - double(Sr[1]), 1.0 / 3.0, (d1 - d2) * (1.0 / 12.0));
   };
   double gTx, gTy, gpx, gpy;
   grad(tS, tC, tN, &gTx, &gTy);
   grad(pS, pC, pN, &gpx, &gpy);
   if (DEV) gTy += a.Tg;   // the stencil is exact on the linear reference
-  double jxd = 0.0, jyd = 0.0;
+  double fv[9];
 #pragma unroll
-  for (int q = 1; q < 9; ++q) {
-    if (kEx[q] != 0) jxd += double(kEx[q]) * double(cur.v[q]);
-    if (kEy[q] != 0) jyd += double(kEy[q]) * double(cur.v[q]);
-  }
+  for (int q = 0; q < 9; ++q) fv[q] = double(cur.v[q]);
+  const double m5 = fv[5] - fv[7], m6 = fv[6] - fv[8];
+  const double jx = (fv[1] - fv[3]) + (m5 - m6), jy = (fv[2] - fv[4]) + (m5 + m6);
   if (MODE & kTape) {
-    const size_t s = (size_t)j * nx + x;
+    const size_t s = (size_t)j * a.nx + x;
     double *tc = static_cast<double *>(a.tape);
     R *tr = reinterpret_cast<R *>(tc + n);
     tc[s] = cd;
     tr[s] = Tv;
     tr[n + s] = pv;
-    tr[2 * n + s] = R(jxd);
-    tr[3 * n + s] = R(jyd);
+    tr[2 * n + s] = R(jx);
+    tr[3 * n + s] = R(jy);
   }
-  // closures
-  const double Tm = DEV ? double(Tv) + (Trow - a.Tref) : double(Tv) - a.Tref;   // T - Tref
-  const double sigma = a.sigma0 - a.sigmaT * Tm;
-  const double gsx = -a.sigmaT * gTx, gsy = -a.sigmaT * gTy;
-  const double g2 = gcx_d * gcx_d + gcy_d * gcy_d;
-  const double gds = gcx_d * gsx + gcy_d * gsy;
+  // closures: sigma = sigma0 - sigmaT (T - Tref)
+  const double sigma = fma_(-a.sigmaT, double(Tv) + (Trow - a.Tref), a.sigma0);
   // capillary part along grad c: kcap sigma mu (potential form) or
   // -sigma eps alpha |grad c| div n (curvature form)
-  const double ks = (MODE & kCurv) ? -a.epsalpha * sigma * tHt : a.kcap * sigma * mu_d;
+  const double ks = (MODE & kCurv) ? -a.epsalpha * sigma * tHt : a.kcap * sigma * mu;
+  // Marangoni part, grad sigma = -sigmaT grad T
+  const double mg = a.epsT * fma_(gcx, gTy, -(gcy * gTx));
   // two densities: rho(c) = rho + c drho, grad rho = drho grad c
-  const double rho_s = VR ? a.rho + cd * a.drho : a.rho;
-  const double grx = VR ? a.drho * gcx_d : 0.0, gry = VR ? a.drho * gcy_d : 0.0;
-  const double inv_rho = 1.0 / rho_s;
-  const double Fxd = ks * gcx_d + a.epsalpha * (g2 * gsx - gds * gcx_d) + rho_s * a.ax;
-  const double Fyd = ks * gcy_d + a.epsalpha * (g2 * gsy - gds * gcy_d) + rho_s * a.ay;
-  const double uxd = 3.0 * jxd * inv_rho + 0.5 * Fxd * inv_rho;
-  const double uyd = 3.0 * jyd * inv_rho + 0.5 * Fyd * inv_rho;
+  const double rho_s = VR ? fma_(cd, a.drho, a.rho) : a.rho;
+  const double inv_rho = VR ? 1.0 / rho_s : a.inv_rho;
+  const double Fx = fma_(ks, gcx, fma_(mg, gcy, rho_s * a.ax));
+  const double Fy = fma_(ks, gcy, fma_(-mg, gcx, rho_s * a.ay));
+  // u = (3 j + F / 2) / rho
+  const double uxd = fma_(0.5, Fx, 3.0 * jx) * inv_rho, uyd = fma_(0.5, Fy, 3.0 * jy) * inv_rho;
+  const double grx = VR ? a.drho * gcx : 0.0, gry = VR ? a.drho * gcy : 0.0;
   if (MODE & kPress) {
     // the pressure of Eq. 9: p = sum f + (1/2) u.grad(rho cs^2)
-    a.pc_out[(size_t)j * nx + x] = double(pv) + (0.5 / 3.0) * (uxd * grx + uyd * gry);
+    a.pc_out[(size_t)j * a.nx + x] = fma_(0.5 / 3.0, fma_(uxd, grx, uyd * gry), double(pv));
     return;
   }
-  const R ux = R(uxd), uy = R(uyd);
-  // F - grad p drives c (Eq. 12); F-bar = grad(rho cs^2) - grad p + F
-  // drives hbar (Sec. III)
-  const R Fbx = R(Fxd - gpx), Fby = R(Fyd - gpy);
-  const R Fhx = VR ? R(Fxd - gpx + grx / 3.0) : Fbx, Fhy = VR ? R(Fyd - gpy + gry / 3.0) : Fby;
-
   if (MODE & kDiag) {
     const double Td = DEV ? double(Tv) + Trow : double(Tv);
     const double yy = double(j) + 0.5, xx = double(x) + 0.5;
     acc[0] += cd;
-    acc[1] += (VR ? rho_s * a.cv : a.rcv) * Td;
-    acc[2] += cd * yy;
-    acc[3] += cd * xx;
+    acc[1] = fma_(VR ? rho_s * a.cv : a.rcv, Td, acc[1]);
+    acc[2] = fma_(cd, yy, acc[2]);
+    acc[3] = fma_(cd, xx, acc[3]);
     if (cd >= 0.5) {
       acc[4] += cd;
-      acc[5] += cd * double(uy);
+      acc[5] = fma_(cd, double(R(uyd)), acc[5]);
     }
-    const double chk = cd + Td + double(pv) + double(ux) + double(uy);
+    const double chk = cd + Td + double(pv) + double(R(uxd)) + double(R(uyd));
     if (!isfinite(chk)) acc[6] += 1.0;
   }
   if (MODE & kFields) {
-    const size_t s = (size_t)j * nx + x;
-    if (a.phi) a.phi[s] = 2.0 * cd - 1.0;
-    if (a.ux) a.ux[s] = double(ux);
-    if (a.uy) a.uy[s] = double(uy);
+    const size_t s = (size_t)j * a.nx + x;
+    if (a.phi) a.phi[s] = fma_(2.0, cd, -1.0);
+    if (a.ux) a.ux[s] = double(R(uxd));
+    if (a.uy) a.uy[s] = double(R(uyd));
     if (a.p) a.p[s] = DEV ? double(pv) + a.p0 : double(pv);
     if (a.T) a.T[s] = DEV ? double(Tv) + Trow : double(Tv);
   }
-  if (MODE & kStore) {
-    // one descriptor for the whole destination state (below 4 GiB); a
-    // plane's segment within a row is selected by a scalar offset
-    const __amdgpu_buffer_rsrc_t rd = plane_rsrc(a.dst, state_bytes_for<S>(n));
-    const uint32_t pbytes = (uint32_t)(nx * sizeof(S));   // a plane's segment of a row
-    const uint32_t RB = (uint32_t)row_bytes<S>(nx);
+  if (!(MODE & kStore)) return;
+
+  // relaxation: rates om = 1/tau and the forcing factors tau - 1/2, times
+  // 3/rho in the g and hbar equations (F enters as F/(rho cs^2))
+  const R c = R(cd);
+  double omf = a.omf, chf = a.chf;
+  R omT = k.omT, chT = k.chT;
+  if (a.vartau) {
     const R ch = c < R(0) ? R(0) : (c > R(1) ? R(1) : c);
-    const double wfd = 1.0 / (a.tauf0 + double(ch) * a.dtauf), cfd = 1.0 - 0.5 * wfd;
-    const double usqd = uxd * uxd + uyd * uyd;
-    const R wT = R(1) / (k.tauT0 + ch * k.dtauT);
-    const R wg = k.wg;
-    const R usq = ux * ux + uy * uy;
-    // temperature in FP64 for the rest population, in R for the others
-    double hs = 0.0;
-#pragma unroll
-    for (int q = 1; q < 9; ++q) hs += double(cur.v[18 + q]);
-    const double rcv_s = VR ? rho_s * a.cv : a.rcv;
-    // two densities, FP32 form: the deviations are taken from w rho cv Trow
-    // with the density of the c = 0 fluid; hoff = (rho(c) - rho) cv Trow
-    const double hoff_d = (VR && DEV) ? cd * a.drho * a.cv * Trow : 0.0;
-    const double Td = (cur.h0() + hs - hoff_d) / rcv_s;   // T or Delta T, FP64
-    const double Tfull_d = DEV ? Td + Trow : Td;
-    const R Tfull = R(Tfull_d);
-    const R rcvT = (VR ? R(rcv_s) : k.rcv) * Tfull;
-    const R gmu = R(a.gam3 * mu_d);
-    const R cgf = R(1) - R(0.5) * wg, chf = R(1) - R(0.5) * wT;
-    const R irho = VR ? R(inv_rho) : k.inv_rho;
-    const R src_g = R(3) * c * irho;          // c / (rho cs^2)
-    const R src_h = R(3) * irho;              // 1 / (rho cs^2)
-    const bool walls = a.walls_y != 0;
-    const bool bot = walls && j == 0, top = walls && j == ny - 1;
-    const uint32_t own = (uint32_t)j * RB;   // this row's offset
-    // value of plane q to site (xs, row) (row_off = row * RB)
-    auto st = [&](int q, int row, uint32_t row_off, int xs, R val) {
-      if constexpr (LDSOUT)
-        *reinterpret_cast<S *>(lds_dst + lds_plane_off<S>(plane_of(q), n) +
-                               ((size_t)row * nx + xs) * sizeof(S)) = S(val);
-      else
-        buf_store<S>(S(val), rd, row_off + (uint32_t)xs * (uint32_t)sizeof(S),
-                     (uint32_t)plane_of(q) * pbytes);
-    };
-    // stores whose lines this wave writes whole
-    constexpr bool stream = (MODE & kStream) != 0;
-    auto st_whole = [&](int q, int row, uint32_t row_off, int xs, R val) {
-      const uint32_t off = row_off + (uint32_t)xs * (uint32_t)sizeof(S);
-      if constexpr (LDSOUT)
-        *reinterpret_cast<S *>(lds_dst + lds_plane_off<S>(plane_of(q), n) +
-                               ((size_t)row * nx + xs) * sizeof(S)) = S(val);
-      else if constexpr (stream)
-        buf_store_stream<S>(S(val), rd, off, (uint32_t)plane_of(q) * pbytes);
-      else
-        buf_store<S>(S(val), rd, off, (uint32_t)plane_of(q) * pbytes);
-    };
-    // FP32 form: what the eight moving populations of g and hbar give away in
-    // this collision, as stored (sum of old - new, each difference of two
-    // nearby FP32 values)
-    R dg = 0, dh = 0;
-    R gsrc0 = 0, hsrc0 = 0, G0 = 0, gam0 = 0;
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-      const R w = wq<R>(i);
-      const R e = R(kEx[i]) * ux + R(kEy[i]) * uy;
-      const R G = w * (R(3) * e + R(4.5) * e * e - R(1.5) * usq);  // Gamma_i - w_i
-      const R gam = w + G;
-      const R cxu = R(kEx[i]) - ux, cyu = R(kEy[i]) - uy;
-      const R fbe = Fbx * cxu + Fby * cyu;
-      const R fhe = VR ? Fhx * cxu + Fhy * cyu : fbe;
-      // f (Eqs. 6-7): f^eq = w p + rho cs^2 G, in FP64.  Near an interface
-      // the forcing term carries the capillary force, which the pressure
-      // gradient balances; FP32 weights and Gamma_i would leave a relative
-      // bias of ~1e-8 in that balance, a spurious force whose viscous
-      // response grows over R^2 / nu steps.
-      const double wd = wq<double>(i);
-      const double ed = double(kEx[i]) * uxd + double(kEy[i]) * uyd;
-      const double Gd = wd * (3.0 * ed + 4.5 * ed * ed - 1.5 * usqd);
-      const double fed = Fxd * (double(kEx[i]) - uxd) + Fyd * (double(kEy[i]) - uyd);
-      const double feqd = wd * double(pv) + rho_s * (1.0 / 3.0) * Gd;
-      const double vd = double(cur.v[i]);
-      // with two densities the forcing adds (xi - u).grad(rho cs^2)
-      // (Gamma_i(u) - Gamma_i(0)) (Eq. 6); Gamma_i(0) = w_i
-      const double srcf = VR ? fed * (wd + Gd) +
-                                   (1.0 / 3.0) * (grx * (double(kEx[i]) - uxd) +
-                                                  gry * (double(kEy[i]) - uyd)) * Gd
-                             : fed * (wd + Gd);
-      const R fo = R(vd - wfd * (vd - feqd) + cfd * srcf);
-      // g (Eqs. 12-14): g^eq_0 = c - (1 - w0) 3 Gamma mu + c G_0,
-      //                 g^eq_i = w_i 3 Gamma mu + c G_i
-      const R gsrc = cgf * src_g * fbe * gam;
-      // hbar (Eqs. 22, 25): h^eq = rho cv T Gamma_i
-      const R heq_full = rcvT * gam;
-      const R hsrc = chf * src_h * fhe * heq_full;
-      if (i == 0) {
-        st_whole(0, j, own, x, fo);
-        gsrc0 = gsrc;
-        hsrc0 = hsrc;
-        G0 = G;
-        gam0 = gam;
-        continue;
-      }
-      const R geq = w * gmu + c * G;
-      const R go = cur.v[9 + i] - wg * (cur.v[9 + i] - geq) + gsrc;
-      R heq;
-      if constexpr (DEV && VR)
-        heq = R(rcv_s) * (Tv * w + Tfull * G) + w * R(hoff_d);
-      else
-        heq = DEV ? k.rcv * (Tv * w + Tfull * G) : heq_full;
-      const R ho = cur.v[18 + i] - wT * (cur.v[18 + i] - heq) + hsrc;
-      dg += cur.v[9 + i] - go;
-      // push to x + xi_i
-      const bool out = (kEy[i] < 0 && bot) || (kEy[i] > 0 && top);
-      if (out) {
-        // reflected into the opposite direction at this site
-        const int o = kOpp[i];
-        const double *tw = kEy[i] < 0 ? a.twb : a.twt;
-        const R twv = DEV ? R(tw[x] - Trow) : R(tw[x]);
-        st(o, j, own, x, fo);
-        st(9 + o, j, own, x, go);
-        if constexpr (DEV && VR)
-          st(18 + o, j, own, x, R(2) * w * (R(rcv_s) * twv + R(hoff_d)) - ho);
-        else
-          st(18 + o, j, own, x, R(2) * w * (VR ? R(rcv_s) : k.rcv) * twv - ho);
-        dh += cur.v[18 + i] - ho;
-      } else {
-        int xd = x + kEx[i];
-        xd = xd < 0 ? xd + nx : (xd >= nx ? xd - nx : xd);
-        int yd = j + kEy[i];
-        yd = yd < 0 ? yd + ny : (yd >= ny ? yd - ny : yd);
-        const uint32_t ro = (uint32_t)yd * RB;
-        if (kEx[i] == 0) {
-          st_whole(i, yd, ro, xd, fo);
-          st_whole(9 + i, yd, ro, xd, go);
-        } else {
-          st(i, yd, ro, xd, fo);
-          st(9 + i, yd, ro, xd, go);
-        }
-        // a move to the next row changes the reference by Tg xi_y
-        const R shift = DEV && kEy[i] != 0 ? R(kEy[i]) * w * k.rcv * R(a.Tg) : R(0);
-        const R hst = ho - shift;
-        if (kEx[i] == 0)
-          st_whole(18 + i, yd, ro, xd, hst);
-        else
-          st(18 + i, yd, ro, xd, hst);
-        dh += (cur.v[18 + i] - hst) - shift;
-      }
-    }
-    // rest populations, formed in FP64
-    double gnew, hnew;
-    if (DEV) {
-      // The collision conserves c = sum g and rho cv T = sum hbar at the site,
-      // so the rest populations receive exactly what the eight stored FP32
-      // values gave away: the FP64 g_0 takes up their rounding, and c is
-      // transported without a systematic drift; hbar_0 is then rounded once
-      // to its FP32 deviation.
-      gnew = cur.g0() + double(dg);
-      hnew = cur.h0() + double(dh);
+    const double tf = fma_(double(ch), a.dtauf, a.tauf0);
+    const R tT = fma_(ch, k.dtauT, k.tauT0);
+    omf = 1.0 / tf;
+    chf = tf - 0.5;
+    omT = R(1) / tT;
+    chT = (tT - R(0.5)) * k.i3rho;
+  }
+  const R irho_r = VR ? R(inv_rho * a.rho) : R(1);   // two densities: rho / rho(c)
+  const double rcvd = VR ? rho_s * a.cv : a.rcv;
+  const R rcv = VR ? R(rcvd) : k.rcv;
+  // two densities, FP32 form: the deviations are taken from w rho cv Trow
+  // with the density of the c = 0 fluid; hoff = (rho(c) - rho) cv Trow
+  const R hoff = (VR && DEV) ? R(cd * a.drho * a.cv * Trow) : R(0);
+  // a direction that the wall reflects stores 2 w (rho cv T_wall [+ hoff]) -
+  // hbar; elsewhere the value itself (factor 1, wall term 0)
+  R su = 1, wu = 0, sd = 1, wdn = 0;
+  if (WALL && (bot || top)) {
+    const R twv = R((bot ? a.twb : a.twt)[x] - Trow);
+    const R wall = R(2.0 / 36.0) * (VR ? fma_(rcv, twv, hoff) : rcv * twv);
+    if (top) {
+      su = -1;
+      wu = wall;
     } else {
-      // Eqs. 12-14 as printed: g_0 - w_g (g_0 - g^eq_0) with
-      // g^eq_0 = c - (1 - w0) 3 Gamma mu + c G_0 and c = sum g
-      const double w0 = wq<double>(0);
-      const double geq0 = cd - (1.0 - w0) * double(gmu) + cd * double(G0);
-      gnew = cur.g0() - double(wg) * (cur.g0() - geq0) + double(gsrc0);
-      const double hdiff = cur.h0() - rcv_s * Tfull_d * double(gam0);
-      hnew = cur.h0() + double(-wT * R(hdiff) + hsrc0);
-    }
-    if constexpr (LDSOUT) {
-      using T0 = typename RestRaw<rest_fmt<S>(0)>::T;
-      using T1 = typename RestRaw<rest_fmt<S>(1)>::T;
-      const size_t so = (size_t)j * nx + x;
-      *reinterpret_cast<T0 *>(lds_dst + lds_rest_off<S>(0, n) + so * sizeof(T0)) = T0(gnew);
-      *reinterpret_cast<T1 *>(lds_dst + lds_rest_off<S>(1, n) + so * sizeof(T1)) = T1(hnew);
-    } else {
-      rest_store<S, 0, stream>(gnew, rd, own, x, (uint32_t)rest_base<S>(0, nx));
-      rest_store<S, 1, stream>(hnew, rd, own, x, (uint32_t)rest_base<S>(1, nx));
+      sd = -1;
+      wdn = wall;
     }
   }
+
+  // f (Eqs. 6-7) in FP64: f^eq = w p + rho cs^2 G with G = w (b + Q).  Near an
+  // interface the forcing term carries the capillary force, which the
+  // pressure gradient balances; FP32 weights and Gamma_i would leave a
+  // relative bias of ~1e-8 in that balance, a spurious force whose viscous
+  // response grows over R^2 / nu steps.
+  // pairs of directions (1, 3), (2, 4), (5, 7), (6, 8)
+  const double bx = 3.0 * uxd, by = 3.0 * uyd;
+  const double mh = -1.5 * fma_(uxd, uxd, uyd * uyd);
+  const double X0x = chf * Fx, X0y = chf * Fy;
+  const double X0u = fma_(X0x, uxd, X0y * uyd);
+  // with two densities the forcing adds (xi - u).grad(rho cs^2)
+  // (Gamma_i(u) - Gamma_i(0)) (Eq. 6); Gamma_i(0) = w_i
+  const double cr = VR ? chf * (1.0 / 3.0) : 0.0;
+  const double X1x = VR ? fma_(cr, grx, X0x) : X0x, X1y = VR ? fma_(cr, gry, X0y) : X0y;
+  const double X1u = VR ? fma_(X1x, uxd, X1y * uyd) : X0u;
+  const double fK0 = double(pv) - X0u;
+  const double fK1 = (VR ? rho_s * (1.0 / 3.0) : a.rho3) - X1u;
+  const double bf[4] = {bx, by, bx + by, by - bx};
+  const double X0[4] = {X0x, X0y, X0x + X0y, X0y - X0x};
+  const double X1[4] = {X1x, X1y, VR ? X1x + X1y : X0[2], VR ? X1y - X1x : X0[3]};
+  // g (Eqs. 12-14): g^eq_0 = c - (1 - w0) 3 Gamma mu + c G_0,
+  // g^eq_i = w_i 3 Gamma mu + c G_i, forced by F - grad p; hbar (Eqs. 22, 25):
+  // h^eq = rho cv T Gamma_i, forced by Fbar = F - grad p + grad(rho cs^2)
+  const R ux = R(uxd), uy = R(uyd);
+  const R bxr = R(3) * ux, byr = R(3) * uy;
+  const R mhr = R(-1.5) * fma_(ux, ux, uy * uy);
+  const R gmu = R(a.gam3 * mu);
+  const double Bx = Fx - gpx, By = Fy - gpy;
+  const R Tfull = DEV ? R(double(Tv) + Trow) : Tv;
+  const R rcvT = rcv * Tfull;
+  const R chg = VR ? k.chg * c * irho_r : k.chg * c;
+  const R chh = VR ? chT * rcvT * irho_r : chT * rcvT;
+  const R Gx = chg * R(Bx), Gy = chg * R(By);
+  const R Hx = chh * (VR ? R(fma_(grx, 1.0 / 3.0, Bx)) : R(Bx));
+  const R Hy = chh * (VR ? R(fma_(gry, 1.0 / 3.0, By)) : R(By));
+  const R Gu = fma_(Gx, ux, Gy * uy), Hu = fma_(Hx, ux, Hy * uy);
+  const R gK0 = gmu - Gu, gK1 = c - Gu;
+  const R hK0 = DEV ? (VR ? fma_(rcv, Tv, hoff) - Hu : fma_(rcv, Tv, -Hu)) : rcvT - Hu;
+  const R hK1 = rcvT - Hu;
+  const R b[4] = {bxr, byr, bxr + byr, byr - bxr};
+  const R XG[4] = {Gx, Gy, Gx + Gy, Gy - Gx};
+  const R XH[4] = {Hx, Hy, Hx + Hy, Hy - Hx};
+  // FP32 form: a move to the next row changes the reference of hbar by
+  // w rho cv Tg xi_y (not for the populations that a wall reflects)
+  const R sup = DEV && !(WALL && top) ? k.shift : R(0);
+  const R sdn = DEV && !(WALL && bot) ? -k.shift : R(0);
+  // FP32 form: what the eight moving populations of g and hbar give away in
+  // this collision, as stored (sum of old - new, each difference of two
+  // nearby FP32 values)
+  R dg = 0, dh = 0;
+  auto emit_f = [&](int i, double eq) { sink(i, 0, R(relax(fv[i], wq<double>(i), eq, omf))); };
+  // g and hbar of one direction; eg and eh receive what they give away
+  auto emit_gh = [&](int i, R ge, R he, R &eg, R &eh) {
+#pragma clang fp contract(off)
+    const R w = wq<R>(i), gv = cur.v[9 + i], hv = cur.v[18 + i];
+    const R gn = relax(gv, w, ge, k.omg);
+    R hn = relax(hv, w, he, omT);
+    if (DEV) {
+      eg = gv - gn;
+      if (kEy[i] != 0) {
+        const R sh = (kEy[i] > 0 ? sup : sdn) * (i < 5 ? R(4) : R(1));   // w = 4/36 or 1/36
+        hn -= sh;
+        eh = (hv - hn) - sh;
+      } else {
+        eh = hv - hn;
+      }
+    }
+    sink(i, 1, gn);
+    if (!WALL || kEy[i] == 0)
+      sink(i, 2, hn);
+    else
+      sink(i, 2, fma_(kEy[i] > 0 ? su : sd, hn, (kEy[i] > 0 ? wu : wdn) * (i < 5 ? R(4) : R(1))));
+  };
+  auto give = [&](R eg, R eh) {
+#pragma clang fp contract(off)
+    if (DEV) {
+      dg += eg;
+      dh += eh;
+    }
+  };
+  auto eq_f = [&](int m) {
+    return pair_eq(bf[m], fma_(0.5 * bf[m], bf[m], mh), fK0, fK1, X0[m], VR ? X1[m] : X0[m]);
+  };
+  auto Q_of = [&](int m) { return fma_(R(0.5) * b[m], b[m], mhr); };
+  auto eq_g = [&](int m, R Q) { return pair_eq(b[m], Q, gK0, gK1, XG[m], XG[m]); };
+  auto eq_h = [&](int m, R Q) { return pair_eq(b[m], Q, hK0, hK1, XH[m], XH[m]); };
+  constexpr int first[4] = {1, 2, 5, 6};   // of a pair; the opposite direction is two on
+  sink(0, 0, R(relax(fv[0], wq<double>(0), fma_(mh, fK1, fK0), omf)));
+  if constexpr (BYDIR) {
+#pragma unroll
+    for (int m0 = 0; m0 < 4; m0 += 2) {
+      PairEq<double> f[2];
+      PairEq<R> g[2], h[2];
+      R eg[2][2] = {}, eh[2][2] = {};
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int m = m0 + t;
+        const R Q = Q_of(m);
+        f[t] = eq_f(m);
+        g[t] = eq_g(m, Q);
+        h[t] = eq_h(m, Q);
+        emit_f(first[m], f[t].E + f[t].O);
+        emit_gh(first[m], g[t].E + g[t].O, h[t].E + h[t].O, eg[t][0], eh[t][0]);
+      }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) {
+        const int m = m0 + t;
+        emit_f(first[m] + 2, f[t].E - f[t].O);
+        emit_gh(first[m] + 2, g[t].E - g[t].O, h[t].E - h[t].O, eg[t][1], eh[t][1]);
+        // pair by pair in either order, so that the bits are the same
+        give(eg[t][0], eh[t][0]);
+        give(eg[t][1], eh[t][1]);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      const PairEq<double> f = eq_f(m);
+      emit_f(first[m], f.E + f.O);
+      emit_f(first[m] + 2, f.E - f.O);
+      const R Q = Q_of(m);
+      const PairEq<R> g = eq_g(m, Q), h = eq_h(m, Q);
+      R eg = 0, eh = 0;
+      emit_gh(first[m], g.E + g.O, h.E + h.O, eg, eh);
+      give(eg, eh);
+      emit_gh(first[m] + 2, g.E - g.O, h.E - h.O, eg, eh);
+      give(eg, eh);
+    }
+  }
+  // rest populations, formed in FP64
+  if (DEV) {
+    // The collision conserves c = sum g and rho cv T = sum hbar at the site,
+    // so the rest populations receive exactly what the eight stored FP32
+    // values gave away: the FP64 g_0 takes up their rounding, and c is
+    // transported without a systematic drift; hbar_0 is then rounded once
+    // to its FP32 deviation.
+    sink.rest(cur.g0() + double(dg), cur.h0() + double(dh));
+  } else {
+    // Eqs. 12-14 as printed, term by term, g^eq_0 formed from c = sum g and the
+    // forcing added last: this value carries c, and its rounding is the one
+    // the planar Marangoni velocity is sensitive to over tens of thousands of
+    // steps (folding the forcing into the relaxation drifted from the printed
+    // form by 1.7e-10 of the velocity in 50,000 steps)
+    const double w0 = wq<double>(0), G0 = w0 * double(mhr);
+    const double geq0 = fma_(cd, G0, fma_(-(1.0 - w0), double(gmu), cd));
+    sink.rest(fma_(-double(k.omg), cur.g0() - geq0, cur.g0()) - double(k.omg * Gu) * (w0 + G0),
+              relax(cur.h0(), w0, double(fma_(mhr, hK1, hK0)), double(omT)));
+  }
+}
+
+// Streams a site's values to a state in global memory, for kernels whose
+// waves each hold one row: the row and the walls are then wave-uniform, so a
+// store's row, plane and reflection are its scalar offset and the lane holds
+// three columns.  Push to x + xi (x periodic); at a wall into the opposite
+// direction at the site itself.
+template <typename S, bool STREAM>
+struct RowSink {
+  __amdgpu_buffer_rsrc_t rd;
+  uint32_t pb;                   // a plane's segment of a row
+  uint32_t own, up, down;        // row offsets
+  uint32_t rb0, rb1;
+  uint32_t xo[3];                // byte offsets of the columns x - 1, x, x + 1
+  int x;
+  bool bot, top;
+  __device__ __forceinline__ RowSink(const StepArgs &a, int j, int x_, bool bot_, bool top_)
+      : x(x_), bot(bot_), top(top_) {
+    const size_t n = (size_t)a.nx * (size_t)a.ny;
+    const uint32_t RB = (uint32_t)row_bytes<S>(a.nx);
+    // one descriptor for the whole destination state (below 4 GiB)
+    rd = plane_rsrc(a.dst, state_bytes_for<S>(n));
+    pb = (uint32_t)(a.nx * sizeof(S));
+    own = (uint32_t)j * RB;
+    up = (j + 1 == a.ny ? 0u : (uint32_t)(j + 1)) * RB;
+    down = (uint32_t)(j == 0 ? a.ny - 1 : j - 1) * RB;
+    rb0 = (uint32_t)rest_base<S>(0, a.nx);
+    rb1 = (uint32_t)rest_base<S>(1, a.nx);
+    xo[0] = (uint32_t)(x == 0 ? a.nx - 1 : x - 1) * (uint32_t)sizeof(S);
+    xo[1] = (uint32_t)x * (uint32_t)sizeof(S);
+    xo[2] = (uint32_t)(x + 1 == a.nx ? 0 : x + 1) * (uint32_t)sizeof(S);
+  }
+  template <typename R>
+  __device__ __forceinline__ void operator()(int i, int lat, R v) const {
+    const bool out = (kEy[i] > 0 && top) || (kEy[i] < 0 && bot);
+    const uint32_t row = kEy[i] == 0 ? own : (kEy[i] > 0 ? up : down);
+    const uint32_t so = out ? own + (uint32_t)plane_of(9 * lat + kOpp[i]) * pb
+                            : row + (uint32_t)plane_of(9 * lat + i) * pb;
+    const uint32_t vo = out ? xo[1] : xo[1 + kEx[i]];
+    if (STREAM && kEx[i] == 0)   // a line that this wave writes whole
+      buf_store_stream<S>(S(v), rd, vo, so);
+    else
+      buf_store<S>(S(v), rd, vo, so);
+  }
+  __device__ __forceinline__ void rest(double g0, double h0) const {
+    rest_store<S, 0, STREAM>(g0, rd, 0u, x, own + rb0);
+    rest_store<S, 1, STREAM>(h0, rd, 0u, x, own + rb1);
+  }
+};
+
+// the collision and stores of a site whose wave holds row j
+template <typename S, typename R, bool DEV, int MODE>
+__device__ __forceinline__ void site_update(const StepArgs &a, int j, int x, const double *cS,
+                                            const double *cC, const double *cN, const R *tS,
+                                            const R *tC, const R *tN, const R *pS, const R *pC,
+                                            const R *pN, const RowVals<R> &cur, double *acc) {
+  const bool bot = a.walls_y != 0 && j == 0, top = a.walls_y != 0 && j == a.ny - 1;
+  site_collide<R, DEV, MODE, true, true>(a, j, x, bot, top, cS, cC, cN, tS, tC, tN, pS, pC, pN, cur, acc,
+                             RowSink<S, (MODE & kStream) != 0>(a, j, x, bot, top));
 }
 
 // deterministic block reduction of the per-lane diagnostic sums: fixed
@@ -542,8 +630,7 @@ step_kernel(const StepArgs a) {
   const int y1 = min(y0 + a.rows_per_chunk, ny);
   const size_t n = (size_t)nx * (size_t)ny;
   const S *__restrict__ src = static_cast<const S *>(a.src);
-  const Consts<R> k(a);
-  const double inv_rcv = 1.0 / a.rcv;
+  const double inv_rcv = a.inv_rcv;
 
   // helper lanes: 0..2 sum the left halo column's c, T, p, 3..5 the right
   // one's.  Eight-wave strips and the FP64 step spread them over the waves
@@ -756,7 +843,7 @@ step_kernel(const StepArgs a) {
     }
     if (act) {
       const int l = lane;
-      site_update<S, R, DEV, MODE>(a, k, j, x, &ringc[(j - 1) & 3][l], &ringc[j & 3][l],
+      site_update<S, R, DEV, MODE>(a, j, x, &ringc[(j - 1) & 3][l], &ringc[j & 3][l],
                                    &ringc[(j + 1) & 3][l], &ringt[(j - 1) & 3][l],
                                    &ringt[j & 3][l], &ringt[(j + 1) & 3][l],
                                    &ringp[(j - 1) & 3][l], &ringp[j & 3][l],
@@ -796,6 +883,57 @@ step_kernel(const StepArgs a) {
 // it in.  Blocks of at most kSmallMaxSites (512) lanes leave each lane twice
 // the registers of a 1024-lane block, enough for the collision without
 // spilling.
+//
+// SmallSink streams a site of it: lanes of one wave hold several rows, so
+// every lane has its own addresses.
+template <typename S, bool RES>
+struct SmallSink {
+  char *dst;        // RES: a state in LDS, else the row-interleaved global state
+  int nx, j, x;
+  size_t n;
+  uint32_t RB, pb, rb0, rb1;
+  int xs[3], ys[3];
+  bool bot, top;
+  __device__ __forceinline__ SmallSink(const StepArgs &a, char *d, int j_, int x_, bool b, bool t)
+      : dst(d), nx(a.nx), j(j_), x(x_), bot(b), top(t) {
+    n = (size_t)nx * (size_t)a.ny;
+    RB = (uint32_t)row_bytes<S>(nx);
+    pb = (uint32_t)(nx * sizeof(S));
+    rb0 = (uint32_t)rest_base<S>(0, nx);
+    rb1 = (uint32_t)rest_base<S>(1, nx);
+    xs[0] = x == 0 ? nx - 1 : x - 1;
+    xs[1] = x;
+    xs[2] = x + 1 == nx ? 0 : x + 1;
+    ys[0] = j == 0 ? a.ny - 1 : j - 1;
+    ys[1] = j;
+    ys[2] = j + 1 == a.ny ? 0 : j + 1;
+  }
+  __device__ __forceinline__ void put(int plane, int y, int xx, S v) const {
+    if constexpr (RES)
+      *reinterpret_cast<S *>(dst + lds_plane_off<S>(plane, n) + (uint32_t)(y * nx + xx) * sizeof(S)) = v;
+    else
+      *reinterpret_cast<S *>(dst + (uint32_t)y * RB + (uint32_t)plane * pb + (uint32_t)xx * sizeof(S)) = v;
+  }
+  template <typename R>
+  __device__ __forceinline__ void operator()(int i, int lat, R v) const {
+    const bool out = (kEy[i] > 0 && top) || (kEy[i] < 0 && bot);
+    if (out) put(plane_of(9 * lat + kOpp[i]), j, x, S(v));
+    else put(plane_of(9 * lat + i), ys[1 + kEy[i]], xs[1 + kEx[i]], S(v));
+  }
+  __device__ __forceinline__ void rest(double g0, double h0) const {
+    using T0 = typename RestRaw<rest_fmt<S>(0)>::T;
+    using T1 = typename RestRaw<rest_fmt<S>(1)>::T;
+    if constexpr (RES) {
+      const uint32_t so = (uint32_t)(j * nx + x);
+      *reinterpret_cast<T0 *>(dst + lds_rest_off<S>(0, n) + so * sizeof(T0)) = T0(g0);
+      *reinterpret_cast<T1 *>(dst + lds_rest_off<S>(1, n) + so * sizeof(T1)) = T1(h0);
+    } else {
+      char *r = dst + (uint32_t)j * RB;
+      reinterpret_cast<T0 *>(r + rb0)[x] = T0(g0);
+      reinterpret_cast<T1 *>(r + rb1)[x] = T1(h0);
+    }
+  }
+};
 template <typename S, typename R, bool DEV, int MODE, bool RES>
 __global__ void __launch_bounds__(kSmallMaxSites)
 small_step_kernel(const StepArgs a0, void *other, int nsteps) {
@@ -810,8 +948,7 @@ small_step_kernel(const StepArgs a0, void *other, int nsteps) {
   R *lp = lt + (size_t)H * W;                          // [H][W] p (or Delta p)
   const bool walls = a0.walls_y != 0;
   const size_t n = (size_t)nx * (size_t)ny;
-  const Consts<R> k(a0);
-  const double inv_rcv = 1.0 / a0.rcv;
+  const double inv_rcv = a0.inv_rcv;
   const uint32_t pbytes = (uint32_t)(nx * sizeof(S));   // a plane's segment of a row
   const uint32_t RB = (uint32_t)row_bytes<S>(nx);
   const uint32_t rb0 = (uint32_t)rest_base<S>(0, nx), rb1 = (uint32_t)rest_base<S>(1, nx);
@@ -911,9 +1048,11 @@ small_step_kernel(const StepArgs a0, void *other, int nsteps) {
       RowVals<R> cur;
       load_site(y, x, cur);
       const size_t rS = (size_t)y * W + x, rC = rS + W, rN = rC + W;
-      site_update<S, R, DEV, MODE, RES>(a, k, y, x, lc + rS, lc + rC, lc + rN, lt + rS,
-                                        lt + rC, lt + rN, lp + rS, lp + rC, lp + rN, cur, acc,
-                                        ldst);
+      const bool bot = walls && y == 0, top = walls && y == ny - 1;
+      site_collide<R, DEV, MODE, true, false>(a, y, x, bot, top, lc + rS, lc + rC, lc + rN, lt + rS, lt + rC,
+                                 lt + rN, lp + rS, lp + rC, lp + rN, cur, acc,
+                                 SmallSink<S, RES>(a, RES ? ldst : static_cast<char *>(dstp), y, x,
+                                                   bot, top));
     }
     __syncthreads();
     const void *t = srcp;
@@ -970,13 +1109,14 @@ tile_step_kernel(const StepArgs a) {
   const int nx = a.nx, ny = a.ny;
   const bool walls = a.walls_y != 0;
   const size_t n = (size_t)nx * (size_t)ny;
-  const Consts<R> k(a);
-  const double inv_rcv = 1.0 / a.rcv;
+  const double inv_rcv = a.inv_rcv;
   const int ntx = (nx + kTileX - 1) / kTileX;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int x0 = (tile % ntx) * kTileX, y0 = (tile / ntx) * kTileY;
   const int tid = threadIdx.x;
-  const int lx = tid % kTileX, ly = tid / kTileX;
+  // a wave holds one row of the tile
+  static_assert(kTileX == 64, "one wave per tile row");
+  const int lx = tid & 63, ly = __builtin_amdgcn_readfirstlane(tid >> 6);
   const __amdgpu_buffer_rsrc_t rsrc = plane_rsrc(a.src, state_bytes_for<S>(n));
   const uint32_t pbytes = (uint32_t)(nx * sizeof(S));   // a plane's segment of a row
   const uint32_t RB = (uint32_t)row_bytes<S>(nx);
@@ -1000,8 +1140,8 @@ tile_step_kernel(const StepArgs a) {
   auto cell_of = [&](int cx, int cy) {
     Cell c;
     int gx = x0 - 1 + cx, gy = y0 - 1 + cy;
-    gx %= nx;
-    c.sx = gx < 0 ? gx + nx : gx;
+    if (nx < W) gx %= nx;   // a grid narrower than the tile wraps more than once
+    c.sx = gx < 0 ? gx + nx : (gx >= nx ? gx - nx : gx);
     c.ghost = 0;
     if (walls && gy < 0) {
       c.sy = 0;
@@ -1010,8 +1150,8 @@ tile_step_kernel(const StepArgs a) {
       c.sy = ny - 1;
       c.ghost = 1;
     } else {
-      gy %= ny;
-      c.sy = gy < 0 ? gy + ny : gy;
+      if (ny < H) gy %= ny;
+      c.sy = gy < 0 ? gy + ny : (gy >= ny ? gy - ny : gy);
     }
     return c;
   };
@@ -1080,7 +1220,7 @@ tile_step_kernel(const StepArgs a) {
   const bool wrap = tail > 0 && tail <= 8 && (ntx == 2 || ntx == 4);
   if (y < ny && (x < nx || wrap)) {
     const int rS = ly * W + lx, rC = rS + W, rN = rC + W;
-    site_update<S, R, DEV, MODE>(a, k, y, x < nx ? x : x % nx, lc + rS, lc + rC, lc + rN,
+    site_update<S, R, DEV, MODE>(a, y, x < nx ? x : x % nx, lc + rS, lc + rC, lc + rN,
                                  lt + rS, lt + rC, lt + rN, lp + rS, lp + rC, lp + rN, cur, acc);
     if ((MODE & kDiag) && x >= nx) {
 #pragma unroll

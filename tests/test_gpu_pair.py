@@ -1,0 +1,59 @@
+"""The kernel that takes two plain steps per launch (pair_step_kernel) against
+one launch per step, through the C ABI: the states bitwise the same."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_1412_6238_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lbe():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1412_6238_amd import lbe_csf
+    return lbe_csf
+
+
+# grids around the strips of 56 columns and chunks of few rows: one strip, one
+# column past it, strips of unequal width, chunks of one row, a last chunk that
+# ends next to the top wall, chunks whose cones reach a wall from the rows
+# before, a grid narrower than a strip's margin, periodic in y
+CASES = [(3, 8, 1, 1), (7, 9, 0, 4), (56, 12, 1, 5), (57, 13, 1, 4), (113, 16, 0, 7),
+         (64, 10, 1, 9), (200, 31, 1, 3), (130, 40, 1, 40), (300, 25, 0, 12), (1030, 11, 1, 2)]
+
+
+@pytest.mark.parametrize("nx,ny,walls,rows", CASES)
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_dev"])
+def test_pair_matches_single_steps(lbe, monkeypatch, nx, ny, walls, rows, form, precision):
+    """An odd count and diagnostic steps, so that pairs start at both states,
+    with and without diagnostics, and single steps come in between."""
+    case = wl.random_case(nx, ny, seed=5 * nx + ny, walls_y=walls, n_drops=2, csf_form=form)
+    out = []
+    for pair in ("0", "1"):
+        monkeypatch.setenv("LBE_CSF_PAIR", pair)
+        monkeypatch.setenv("LBE_CSF_PAIR_ROWS", str(rows))
+        monkeypatch.setenv("LBE_CSF_SMALL", "0")
+        print(f"case pair={pair} {nx}x{ny} walls={walls} rows={rows} form={form} {precision}",
+              flush=True)
+        sim = lbe.Simulation(case["params"], case["phi0"], case["T0"],
+                             case["Twall_bot"] if walls else None,
+                             case["Twall_top"] if walls else None, precision=precision,
+                             diag_every=9)
+        sim.step(2)
+        sim.step(11)
+        out.append((sim.get_state().cpu().numpy(), sim.step_count, sim.diag_history()))
+    assert out[0][1] == out[1][1] == 13
+    np.testing.assert_array_equal(out[1][0], out[0][0])
+    # the diagnostics are FP64 sums over other blocks: equal to rounding (at
+    # most nx * ny terms of either sign, each rounded once)
+    assert len(out[0][2]) == len(out[1][2]) == 2
+    for a, b in zip(out[0][2], out[1][2]):
+        assert (a["step"], a["n_nonfinite"]) == (b["step"], b["n_nonfinite"])
+        for k in ("mass", "energy", "sum_cy", "sum_cx"):
+            assert a[k] == pytest.approx(b[k], rel=1e-11), k
+    sys.stdout.flush()
