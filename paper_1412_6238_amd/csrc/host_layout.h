@@ -261,18 +261,30 @@ inline bool two_densities(const lbe_csf_params *p) { return p->rho2 > 0.0 && p->
 // two against 86.0 with four.  One block more than are resident at once would
 // run alone, so the chunks are as many as fit (FP32 eight waves a CU, FP64
 // four, by registers and LDS).
+//
+// Small grids go in tiles (pair_tile_kernel), above 256 sites and while there
+// is a CU for every block.  Measured as above, FP32: 8 x 64 3.7 -> 3.3,
+// 40 x 100 5.0 -> 3.3, 128 x 128 4.8 -> 3.5 (tiles of two rows), 160 x 300
+// 5.7 -> 4.3, 224 x 200 5.4 -> 4.2 (four); FP64: 8 x 64 5.5 -> 3.8, 40 x 100
+// 5.4 -> 3.8, 200 x 100 6.0 -> 4.4, 160 x 300 6.6 -> 5.2.  With more blocks
+// than CUs they lose: 256 x 512 FP32 7.3 -> 9.1, FP64 11.8 -> 13.2, and
+// 160 x 300 FP32 in tiles of two rows (450 blocks) 5.7.  Up to 256 sites one
+// block stepping alone (small_step_kernel) is faster: 8 x 16 2.7.
+constexpr size_t kPairTileMin = 256;
 constexpr int kPairHalo = 4;                    // columns on each side that only feed the others
 constexpr int kPairCols = 64 - 2 * kPairHalo;   // columns a wave owns
 constexpr size_t kPairMaxBytes = 0xffff0000u;   // state size below the dropped stores' offset
 struct PairLaunch {
   int nw, nstrips, rows, nblocks;   // waves a block, strips (one wave each), rows a chunk, blocks
-  int nparts;                       // waves with sites: diagnostic partials
+  int nparts;                       // diagnostic partials
+  int tile;                         // rows of a tile where the pairs go in tiles (pair_tile_kernel)
 };
 inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
-  PairLaunch L{0, 0, 0, 0, 0};
+  PairLaunch L{0, 0, 0, 0, 0, 0};
   const bool fp32 = p->precision == LBE_CSF_FP32_DEV;
   const char *e = std::getenv("LBE_CSF_PAIR");
-  const bool forced = e && std::atoi(e) == 1;
+  const int want = e ? std::atoi(e) : -1;   // 0: single steps, 1: strips and chunks, 2: tiles
+  const bool forced = want > 0;
   if (two_densities(p) || p->ny < 8 || state_bytes > kPairMaxBytes) return L;
   if (e && !forced) return L;
   // the overrides of the one-step kernels ask for those kernels
@@ -280,6 +292,24 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
                         "LBE_CSF_TILE", "LBE_CSF_SMALL"})
     if (!forced && std::getenv(v)) return L;
   const size_t n = (size_t)p->nx * p->ny;
+  const char *rows = std::getenv("LBE_CSF_PAIR_ROWS");
+  // Tiles of 2, 4 or (FP32) 8 rows, the fewest that still give every block a
+  // CU of its own.
+  if (want == 2 || (!forced && n > kPairTileMin)) {
+    const int strips = (p->nx + kPairCols - 1) / kPairCols;
+    const int wx = (p->nx + strips - 1) / strips;
+    L.nstrips = (p->nx + wx - 1) / wx;
+    auto blocks = [&](int ty) { return (long long)L.nstrips * ((p->ny + ty - 1) / ty); };
+    int ty = 2;
+    while (ty < (fp32 ? 8 : 4) && blocks(ty) > kNumCUs) ty *= 2;
+    if (rows && (std::atoi(rows) == 2 || std::atoi(rows) == 4 || (fp32 && std::atoi(rows) == 8)))
+      ty = std::atoi(rows);
+    if (want == 2 || blocks(ty) <= kNumCUs) {
+      L.tile = L.rows = ty;
+      L.nblocks = L.nparts = (int)blocks(ty);
+      return L;
+    }
+  }
   if (!forced && n < (size_t)(fp32 ? 1100000 : 500000)) return L;
   L.nw = n > 3000000 ? (fp32 ? 8 : 4) : (fp32 ? 1 : 2);
   const int ngroups = ((p->nx + kPairCols - 1) / kPairCols + L.nw - 1) / L.nw;
@@ -289,7 +319,7 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
   L.nstrips = (p->nx + wx - 1) / wx;
   const int chunks = std::max(1, slots / ngroups);
   L.rows = (p->ny + chunks - 1) / chunks;
-  if (const char *r = std::getenv("LBE_CSF_PAIR_ROWS")) L.rows = std::max(1, std::min(p->ny, std::atoi(r)));
+  if (rows) L.rows = std::max(1, std::min(p->ny, std::atoi(rows)));
   const int nchunks = (p->ny + L.rows - 1) / L.rows;
   L.nblocks = ngroups * nchunks;
   L.nparts = L.nstrips * nchunks;

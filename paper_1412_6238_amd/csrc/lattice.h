@@ -98,6 +98,15 @@ __device__ __forceinline__ const SiteConsts<R> &site_consts(const StepArgs &a) {
   else return a.kf;
 }
 
+// Reads one word of every cache line of the arguments, so that the constants
+// that a kernel needs late are in the scalar cache by then instead of being
+// fetched one miss after another; called while the first loads are in flight.
+__device__ __forceinline__ void touch_args(const StepArgs &a) {
+  const uint32_t *w = reinterpret_cast<const uint32_t *>(&a);
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(StepArgs) / 4; i += 16) asm volatile("" ::"s"(w[i]));
+}
+
 // Buffer resources: one descriptor per buffer (scalar registers) and a 32-bit
 // byte offset per lane, so a load or store needs one vector register for its
 // address instead of two.  The third descriptor word 0x00020000 is the CDNA

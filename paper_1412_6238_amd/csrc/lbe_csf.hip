@@ -400,6 +400,20 @@ void launch_pair_as(const lbe_csf *h, const StepArgs &a, bool diag) {
   }
 }
 
+template <typename R, bool DEV, int FORM, int TY>
+void launch_pair_tile(const lbe_csf *h, const StepArgs &a, bool diag) {
+  constexpr int M = kStore | FORM, nt = 64 * (TY + 2 * kPairHalo);
+  const int nb = h->pair.nblocks;
+  if (diag) pair_tile_kernel<R, R, DEV, M | kDiag, TY><<<nb, nt, 0, h->stream>>>(a);
+  else pair_tile_kernel<R, R, DEV, M, TY><<<nb, nt, 0, h->stream>>>(a);
+}
+template <typename R, bool DEV, int FORM>
+void launch_pair_tiles(const lbe_csf *h, const StepArgs &a, bool diag) {
+  if (h->pair.tile == 2) launch_pair_tile<R, DEV, FORM, 2>(h, a, diag);
+  else if (DEV && h->pair.tile == 8) launch_pair_tile<R, DEV, FORM, (DEV ? 8 : 4)>(h, a, diag);
+  else launch_pair_tile<R, DEV, FORM, 4>(h, a, diag);
+}
+
 // Two plain steps in one launch, the first with diagnostics where asked; the
 // state alternates once.
 int launch_pair(lbe_csf *h, bool diag) {
@@ -410,7 +424,12 @@ int launch_pair(lbe_csf *h, bool diag) {
   a.rows_per_chunk = h->pair.rows;
   const bool f64 = h->P.precision == LBE_CSF_FP64, curv = h->P.csf_form == 1;
   const bool wide = h->pair.nw > 2;
-  if (f64 && curv && wide) launch_pair_as<double, false, kCurv, 4>(h, a, diag);
+  if (h->pair.tile > 0) {
+    if (f64 && curv) launch_pair_tiles<double, false, kCurv>(h, a, diag);
+    else if (f64) launch_pair_tiles<double, false, 0>(h, a, diag);
+    else if (curv) launch_pair_tiles<float, true, kCurv>(h, a, diag);
+    else launch_pair_tiles<float, true, 0>(h, a, diag);
+  } else if (f64 && curv && wide) launch_pair_as<double, false, kCurv, 4>(h, a, diag);
   else if (f64 && curv) launch_pair_as<double, false, kCurv, 2>(h, a, diag);
   else if (f64 && wide) launch_pair_as<double, false, 0, 4>(h, a, diag);
   else if (f64) launch_pair_as<double, false, 0, 2>(h, a, diag);
@@ -714,7 +733,9 @@ int lbe_csf_create(const lbe_csf_params *params, void *workspace, size_t bytes,
     // both states in LDS where they fit, else the moments only
     const bool f64 = params->precision == LBE_CSF_FP64;
     const size_t lds_res = small_res_bytes(params), lds = small_lds_bytes(params);
-    if (lds_res > 0 && lds_res <= (size_t)max_lds) {
+    if (h->pair.tile > 0) {
+      // pairs of steps in tiles instead
+    } else if (lds_res > 0 && lds_res <= (size_t)max_lds) {
       const hipError_t e = f64 ? small_attrs<double, double, false, true>(lds_res)
                                : small_attrs<float, float, true, true>(lds_res);
       if (e == hipSuccess) {
@@ -723,7 +744,7 @@ int lbe_csf_create(const lbe_csf_params *params, void *workspace, size_t bytes,
       }
       (void)hipGetLastError();
     }
-    if (h->small_lds == 0 && lds > 0 && lds <= (size_t)max_lds) {
+    if (h->pair.tile == 0 && h->small_lds == 0 && lds > 0 && lds <= (size_t)max_lds) {
       const hipError_t e = f64 ? small_attrs<double, double, false, false>(lds)
                                : small_attrs<float, float, true, false>(lds);
       if (e == hipSuccess) h->small_lds = lds;

@@ -107,34 +107,38 @@ struct PairMidSink {
 constexpr uint32_t kDropped = 0xfffffff0u;
 static_assert(host::kPairMaxBytes <= kDropped);
 
-template <typename S, bool STREAM, bool EDGE>
-struct PairOutSink {
+struct PairOut {
   __amdgpu_buffer_rsrc_t rd;
   uint32_t pb, own, up, down, rb0, rb1;
   uint32_t xo[3], xu[3], xd[3];   // columns x - 1, x, x + 1 in rows j, j + 1, j - 1 (without
                                   // EDGE xo serves all three)
   uint32_t x0, x1;                // rest populations
   bool bot, top;
+};
+template <typename S, bool STREAM, bool EDGE, bool WALL>
+struct PairOutSink {
+  const PairOut &o;
   template <typename V>
   __device__ __forceinline__ void operator()(int i, int lat, V v) const {
-    const bool out = EDGE && ((kEy[i] > 0 && top) || (kEy[i] < 0 && bot));
-    const uint32_t row = kEy[i] == 0 ? own : (kEy[i] > 0 ? up : down);
+    const bool out = WALL && ((kEy[i] > 0 && o.top) || (kEy[i] < 0 && o.bot));
+    const uint32_t row = kEy[i] == 0 ? o.own : (kEy[i] > 0 ? o.up : o.down);
     // planes of direction i: i, 8 + i, 16 + i
-    const uint32_t so = (out ? own + (uint32_t)kOpp[i] * pb : row + (uint32_t)i * pb) + (uint32_t)(8 * lat) * pb;
-    const uint32_t *xs = !EDGE || kEy[i] == 0 ? xo : (kEy[i] > 0 ? xu : xd);
-    const uint32_t vo = out ? xo[1] : xs[1 + kEx[i]];
-    if (STREAM && kEx[i] == 0) buf_store_stream<S>(S(v), rd, vo, so);
-    else buf_store<S>(S(v), rd, vo, so);
+    const uint32_t so = (out ? o.own + (uint32_t)kOpp[i] * o.pb : row + (uint32_t)i * o.pb) +
+                        (uint32_t)(8 * lat) * o.pb;
+    const uint32_t *xs = !EDGE || kEy[i] == 0 ? o.xo : (kEy[i] > 0 ? o.xu : o.xd);
+    const uint32_t vo = out ? o.xo[1] : xs[1 + kEx[i]];
+    if (STREAM && kEx[i] == 0) buf_store_stream<S>(S(v), o.rd, vo, so);
+    else buf_store<S>(S(v), o.rd, vo, so);
   }
   __device__ __forceinline__ void rest(double g, double h) const {
     using T0 = typename RestRaw<rest_fmt<S>(0)>::T;
     using T1 = typename RestRaw<rest_fmt<S>(1)>::T;
     if constexpr (STREAM) {
-      buf_store_stream<T0>(T0(g), rd, x0, own + rb0);
-      buf_store_stream<T1>(T1(h), rd, x1, own + rb1);
+      buf_store_stream<T0>(T0(g), o.rd, o.x0, o.own + o.rb0);
+      buf_store_stream<T1>(T1(h), o.rd, o.x1, o.own + o.rb1);
     } else {
-      buf_store<T0>(T0(g), rd, x0, own + rb0);
-      buf_store<T1>(T1(h), rd, x1, own + rb1);
+      buf_store<T0>(T0(g), o.rd, o.x0, o.own + o.rb0);
+      buf_store<T1>(T1(h), o.rd, o.x1, o.own + o.rb1);
     }
   }
 };
@@ -306,7 +310,7 @@ pair_step_kernel(const StepArgs a) {
       const int sS = slot(j - 1), sC = slot(j), sN = slot(j + 1);
       const bool bot = EDGE && walls && j == 0, top = EDGE && walls && j == ny - 1;
       const int jw = EDGE ? wrap_row(j) : j;
-      PairOutSink<S, STREAM, EDGE> out;
+      PairOut out;
       out.rd = plane_rsrc(a.dst, state_bytes_for<S>(n));
       out.pb = opaque(pb);
       out.own = (uint32_t)jw * RB;
@@ -338,7 +342,8 @@ pair_step_kernel(const StepArgs a) {
       site_collide<R, DEV, kMode, EDGE, false>(
           a, jw, x, bot, top, &l.c[1][sS][lane], &l.c[1][sC][lane], &l.c[1][sN][lane],
           &l.t[1][sS][lane], &l.t[1][sC][lane], &l.t[1][sN][lane], &l.p[1][sS][lane],
-          &l.p[1][sC][lane], &l.p[1][sN][lane], f1, acc, out);
+          &l.p[1][sC][lane], &l.p[1][sN][lane], f1, acc,
+          PairOutSink<S, STREAM, EDGE, EDGE>{out});
     }
   };
   // two rows per turn, so that the rows in registers change roles by name;
@@ -374,6 +379,181 @@ pair_step_kernel(const StepArgs a) {
       for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
       if (lane == 0) out[m] = v;
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Two plain steps in one launch on latency-bound grids.  A step of such a grid
+// is one pass of latency (launch, loads, moments, collision, stores: 5-6 us)
+// whatever its size, and most of the chip idles; here one pass takes two
+// steps, at the price of colliding the margin of each tile again.  A block
+// holds the rows of a tile and four more on each side, one wave a row: as in
+// pair_step_kernel a wave's outer four columns on each side only feed the
+// others.  Moments, collision of F_n into LDS, moments of F_{n+1}, collision
+// into the other state, with a block barrier in between.  Diagnostics (of
+// F_n) may come along.  The states are bitwise those of two single steps.
+template <typename S, typename R, int TY>
+struct PairTileLds {
+  static constexpr int H = TY + 2 * kPairHalo, W = 66;
+  double c[H][W];
+  R t[H][W], p[H][W];
+  S f[24][TY + 6][W];   // moving populations of F_{n+1}, rows 2 .. H - 3 of the block (from 1 on), and
+                        // one row on each side for pushes that no row collects
+  double red[H][kNumPartials];
+};
+
+// F_{n+1} of the tile: pushes into LDS; the rest populations stay with the wave
+template <typename S, typename R, int TY, bool WALL>
+struct PairTileSink {
+  PairTileLds<S, R, TY> &l;
+  int k, row;            // own column in the LDS rows, row of the block
+  bool bot, top;
+  RowVals<R> &f1;        // receives the rest populations
+  template <typename V>
+  __device__ __forceinline__ void operator()(int i, int lat, V v) const {
+    if (i == 0) {
+      f1.v[0] = R(S(v));
+      return;
+    }
+    const bool out = WALL && ((kEy[i] > 0 && top) || (kEy[i] < 0 && bot));
+    const int to = max(0, min(TY + 5, row - 1 + (out ? 0 : kEy[i])));
+    const int d = out ? kOpp[i] : i;
+    l.f[8 * lat + d - 1][to][out ? k : k + kEx[i]] = S(v);
+  }
+  __device__ __forceinline__ void rest(double g, double h) const {
+    f1.g0r = g;
+    f1.h0r = typename RestRaw<rest_fmt<S>(1)>::T(h);
+  }
+};
+
+template <typename S, typename R, bool DEV, int MODE, int TY>
+__global__ void __launch_bounds__(64 * (TY + 2 * kPairHalo))
+pair_tile_kernel(const StepArgs a) {
+  static_assert((MODE & ~(kCurv | kDiag)) == kStore, "pairs of plain steps");
+  constexpr int H = TY + 2 * kPairHalo;
+  constexpr int kMode = MODE & ~kDiag;
+  __shared__ PairTileLds<S, R, TY> l;
+  const int nx = a.nx, ny = a.ny;
+  const bool walls = a.walls_y != 0;
+  const int tile = xcd_tile(blockIdx.x, gridDim.x);
+  const int wx = (nx + a.nstrips - 1) / a.nstrips;
+  const int x0 = (tile % a.nstrips) * wx, w = min(wx, nx - x0);
+  const int y0 = (tile / a.nstrips) * TY, y1 = min(y0 + TY, ny);
+  const int lane = threadIdx.x & 63, k = lane + 1;
+  const int row = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  int x = (x0 - kPairHalo + lane) % nx;
+  x = x < 0 ? x + nx : x;
+  const int r = y0 - kPairHalo + row;   // this wave's row, beyond y0 - 1 and y1 a cone's
+  const bool live = r < y1 + kPairHalo && !(walls && (r < 0 || r >= ny));
+  int jr = r % ny;
+  jr = jr < 0 ? jr + ny : jr;
+  const bool bot = walls && r == 0, top = walls && r == ny - 1;
+  const bool owned = lane >= kPairHalo && lane < kPairHalo + w && r >= y0 && r < y1;
+  const size_t n = (size_t)nx * (size_t)ny;
+  const uint32_t pb = (uint32_t)(nx * sizeof(S));
+  const uint32_t RB = (uint32_t)row_bytes<S>(nx);
+  const uint32_t rb0 = (uint32_t)rest_base<S>(0, nx), rb1 = (uint32_t)rest_base<S>(1, nx);
+  using T0 = typename RestRaw<rest_fmt<S>(0)>::T;
+  using T1 = typename RestRaw<rest_fmt<S>(1)>::T;
+  // moments of the wave's row, and of the row beyond a wall (c and p mirrored,
+  // T_ghost = 2 T_wall - T, deviations against the reference at the wall)
+  auto put = [&](const RowVals<R> &v) {
+    double c, T;
+    R p;
+    site_moments<R, false>(v, a.inv_rcv, &c, &T, &p);
+    l.c[row][k] = c;
+    l.t[row][k] = R(T);
+    l.p[row][k] = p;
+    if (bot || top) {
+      const int g = bot ? row - 1 : row + 1;
+      if (g >= 0 && g < H) {
+        const double twref = DEV ? a.Ts + (bot ? 0.0 : a.Tg * double(ny)) : 0.0;
+        const R twv = R((bot ? a.twb : a.twt)[x] - twref);
+        l.c[g][k] = c;
+        l.t[g][k] = R(2) * twv - R(T);
+        l.p[g][k] = p;
+      }
+    }
+  };
+  RowVals<R> cur;
+  double acc[kNumPartials];
+#pragma unroll
+  for (int m = 0; m < kNumPartials; ++m) acc[m] = 0.0;
+  if (live) {
+    const __amdgpu_buffer_rsrc_t rsrc = plane_rsrc(a.src, state_bytes_for<S>(n));
+    const uint32_t vx = (uint32_t)x * (uint32_t)sizeof(S), ro = (uint32_t)jr * RB;
+#pragma unroll
+    for (int q = 0; q < 27; ++q)
+      if (q != 9 && q != 18) cur.v[q] = R(buf_load<S>(rsrc, vx, ro + (uint32_t)plane_of(q) * pb));
+    cur.g0r = buf_load<T0>(rsrc, (uint32_t)x * (uint32_t)sizeof(T0), ro + rb0);
+    cur.h0r = buf_load<T1>(rsrc, (uint32_t)x * (uint32_t)sizeof(T1), ro + rb1);
+    if (sizeof(S) == 4) touch_args(a);   // FP32 3.63 -> 3.33 us a step on 40 x 100; FP64 no gain
+    put(cur);
+  }
+  // FP32: a wave takes the form with walls only where its own row touches one
+  // (in FP64 the two forms together spill registers)
+  auto collide = [&](auto mode, auto wall, auto &&sink) __attribute__((always_inline)) {
+    site_collide<R, DEV, decltype(mode)::value, decltype(wall)::value, false>(
+        a, jr, x, bot, top, &l.c[row - 1][lane], &l.c[row][lane], &l.c[row + 1][lane],
+        &l.t[row - 1][lane], &l.t[row][lane], &l.t[row + 1][lane], &l.p[row - 1][lane],
+        &l.p[row][lane], &l.p[row + 1][lane], cur, acc, sink);
+  };
+  __syncthreads();
+  if (live && row >= 1 && row < H - 1) {
+    RowVals<R> f1;
+    constexpr std::integral_constant<int, MODE> mode{};
+    if (sizeof(S) == 8 || bot || top)
+      collide(mode, std::true_type{}, PairTileSink<S, R, TY, true>{l, k, row, bot, top, f1});
+    else
+      collide(mode, std::false_type{}, PairTileSink<S, R, TY, false>{l, k, row, bot, top, f1});
+    cur.v[0] = f1.v[0];
+    cur.g0r = f1.g0r;
+    cur.h0r = f1.h0r;
+  }
+  if constexpr ((MODE & kDiag) != 0) {
+#pragma unroll
+    for (int m = 0; m < kNumPartials; ++m)
+      if (!owned) acc[m] = 0.0;
+    block_partials<H>(acc, l.red, threadIdx.x, a.partials + (size_t)blockIdx.x * kNumPartials);
+  }
+  __syncthreads();
+  if (live && row >= 2 && row < H - 2) {
+#pragma unroll
+    for (int q = 1; q < 27; ++q)
+      if (q % 9 != 0) cur.v[q] = R(l.f[8 * (q / 9) + q % 9 - 1][row - 1][k]);
+    put(cur);
+  }
+  __syncthreads();
+  if (live && row >= 3 && row < H - 3) {
+    PairOut out;
+    out.rd = plane_rsrc(a.dst, state_bytes_for<S>(n));
+    out.pb = pb;
+    out.own = (uint32_t)jr * RB;
+    out.up = jr + 1 == ny ? 0u : out.own + RB;
+    out.down = (jr == 0 ? (uint32_t)ny : (uint32_t)jr) * RB - RB;
+    out.rb0 = rb0;
+    out.rb1 = rb1;
+    out.bot = bot;
+    out.top = top;
+    const bool okO = r >= y0 && r < y1, okU = r + 1 >= y0 && r + 1 < y1,
+               okD = r - 1 >= y0 && r - 1 < y1;
+#pragma unroll
+    for (int e = 0; e < 3; ++e) {
+      const int o = lane - kPairHalo + e - 1;
+      int xx = x + e - 1;
+      xx = xx < 0 ? xx + nx : (xx >= nx ? xx - nx : xx);
+      const uint32_t xs = o >= 0 && o < w ? (uint32_t)xx * (uint32_t)sizeof(S) : kDropped;
+      out.xo[e] = okO ? xs : kDropped;
+      out.xu[e] = okU ? xs : kDropped;
+      out.xd[e] = okD ? xs : kDropped;
+    }
+    out.x0 = owned ? (uint32_t)x * (uint32_t)sizeof(T0) : kDropped;
+    out.x1 = owned ? (uint32_t)x * (uint32_t)sizeof(T1) : kDropped;
+    constexpr std::integral_constant<int, kMode> mode{};
+    if (sizeof(S) == 8 || bot || top)
+      collide(mode, std::true_type{}, PairOutSink<S, false, true, true>{out});
+    else
+      collide(mode, std::false_type{}, PairOutSink<S, false, true, false>{out});
   }
 }
 

@@ -565,13 +565,13 @@ struct RowSink {
 };
 
 // the collision and stores of a site whose wave holds row j
-template <typename S, typename R, bool DEV, int MODE>
+template <typename S, typename R, bool DEV, int MODE, bool BYDIR>
 __device__ __forceinline__ void site_update(const StepArgs &a, int j, int x, const double *cS,
                                             const double *cC, const double *cN, const R *tS,
                                             const R *tC, const R *tN, const R *pS, const R *pC,
                                             const R *pN, const RowVals<R> &cur, double *acc) {
   const bool bot = a.walls_y != 0 && j == 0, top = a.walls_y != 0 && j == a.ny - 1;
-  site_collide<R, DEV, MODE, true, true>(a, j, x, bot, top, cS, cC, cN, tS, tC, tN, pS, pC, pN, cur, acc,
+  site_collide<R, DEV, MODE, true, BYDIR>(a, j, x, bot, top, cS, cC, cN, tS, tC, tN, pS, pC, pN, cur, acc,
                              RowSink<S, (MODE & kStream) != 0>(a, j, x, bot, top));
 }
 
@@ -843,7 +843,7 @@ step_kernel(const StepArgs a) {
     }
     if (act) {
       const int l = lane;
-      site_update<S, R, DEV, MODE>(a, j, x, &ringc[(j - 1) & 3][l], &ringc[j & 3][l],
+      site_update<S, R, DEV, MODE, true>(a, j, x, &ringc[(j - 1) & 3][l], &ringc[j & 3][l],
                                    &ringc[(j + 1) & 3][l], &ringt[(j - 1) & 3][l],
                                    &ringt[j & 3][l], &ringt[(j + 1) & 3][l],
                                    &ringp[(j - 1) & 3][l], &ringp[j & 3][l],
@@ -1220,7 +1220,7 @@ tile_step_kernel(const StepArgs a) {
   const bool wrap = tail > 0 && tail <= 8 && (ntx == 2 || ntx == 4);
   if (y < ny && (x < nx || wrap)) {
     const int rS = ly * W + lx, rC = rS + W, rN = rC + W;
-    site_update<S, R, DEV, MODE>(a, y, x < nx ? x : x % nx, lc + rS, lc + rC, lc + rN,
+    site_update<S, R, DEV, MODE, false>(a, y, x < nx ? x : x % nx, lc + rS, lc + rC, lc + rN,
                                  lt + rS, lt + rC, lt + rN, lp + rS, lp + rC, lp + rN, cur, acc);
     if ((MODE & kDiag) && x >= nx) {
 #pragma unroll

@@ -1,4 +1,5 @@
-"""The kernel that takes two plain steps per launch (pair_step_kernel) against
+"""The kernels that take two plain steps per launch (pair_step_kernel in strips
+and chunks, pair_tile_kernel in tiles) against
 one launch per step, through the C ABI: the states bitwise the same."""
 import sys
 
@@ -24,17 +25,22 @@ def lbe():
 # before, a grid narrower than a strip's margin, periodic in y
 CASES = [(3, 8, 1, 1), (7, 9, 0, 4), (56, 12, 1, 5), (57, 13, 1, 4), (113, 16, 0, 7),
          (64, 10, 1, 9), (200, 31, 1, 3), (130, 40, 1, 40), (300, 25, 0, 12), (1030, 11, 1, 2)]
+# ... and around the tiles of 2, 4 or 8 rows: a last tile of one row, tiles
+# whose margin reaches the wall, a periodic grid shorter than tile and margin
+TILES = [(3, 8, 1, 4), (7, 9, 0, 4), (40, 100, 1, 2), (56, 12, 1, 8), (57, 13, 1, 4),
+         (113, 17, 0, 8), (200, 31, 1, 2), (130, 41, 0, 4), (300, 25, 1, 8)]
 
 
-@pytest.mark.parametrize("nx,ny,walls,rows", CASES)
+@pytest.mark.parametrize("kind,nx,ny,walls,rows",
+                         [("1",) + c for c in CASES] + [("2",) + c for c in TILES])
 @pytest.mark.parametrize("form", [0, 1])
 @pytest.mark.parametrize("precision", ["fp64", "fp32_dev"])
-def test_pair_matches_single_steps(lbe, monkeypatch, nx, ny, walls, rows, form, precision):
+def test_pair_matches_single_steps(lbe, monkeypatch, kind, nx, ny, walls, rows, form, precision):
     """An odd count and diagnostic steps, so that pairs start at both states,
     with and without diagnostics, and single steps come in between."""
     case = wl.random_case(nx, ny, seed=5 * nx + ny, walls_y=walls, n_drops=2, csf_form=form)
     out = []
-    for pair in ("0", "1"):
+    for pair in ("0", kind):
         monkeypatch.setenv("LBE_CSF_PAIR", pair)
         monkeypatch.setenv("LBE_CSF_PAIR_ROWS", str(rows))
         monkeypatch.setenv("LBE_CSF_SMALL", "0")
