@@ -7,31 +7,36 @@
 // returns lambda_n = (dF_{n+1}/dF_n)^T lambda_{n+1}.  The cotangent is kept
 // in two parts, lambda_q = D_q + M_{group(q)}: D holds 27 planes and M three
 // (the shares of p = sum f, c = sum g and rho cv T = sum hbar, which reach
-// every population of a group alike).  One adjoint step is two kernels, one
-// thread per site, no recomputation:
-//   adj_collide_kernel  lambda* = Stream^T lambda_{n+1}, a pull from x + xi_i
-//       (at a wall the reflected population of the same site, with the sign
-//       flip of the anti-bounce-back for hbar, whose wall term 2 w rho cv
-//       T_wall gives dJ/dT_wall); then the transpose of the site's collision
-//       (site_adjoint): D_n(x), the stencil cotangents A_n(x) (grad c, lap c,
-//       grad T, grad p) and the site's share of dJ/dsigmaT;
-//   adj_stencil_kernel  the stencil transposes: the moments of site y collect
-//       A_n(x) from every x whose stencil reads y (in the wall rows the ghost
-//       row mirrors c and p and holds 2 T_wall - T, so T collects with a minus
-//       sign and T_wall twice) into M_n(y).
-// The linearisation point (c, T, p, j of F_n) comes from a moment tape that
-// the replay writes; the populations themselves are read only when the
-// relaxation times vary with c.
+// every population of a group alike).  M itself is not kept between steps but
+// the stencil cotangents A it is formed from.  One adjoint step is one kernel
+// (adj_step_kernel), one thread per site:
+//   the stencil transposes: the moments of site y collect A_{n+1}(x) from every
+//       x whose stencil reads y (in the wall rows the ghost row mirrors c and p
+//       and holds 2 T_wall - T, so T collects with a minus sign and T_wall
+//       twice) into M_{n+1}(y), for the sites of a tile and the one around it;
+//   lambda* = Stream^T lambda_{n+1}, a pull from x + xi_i (at a wall the
+//       reflected population of the same site, with the sign flip of the
+//       anti-bounce-back for hbar, whose wall term 2 w rho cv T_wall gives
+//       dJ/dT_wall);
+//   the transpose of the site's collision (site_adjoint): D_n(x), the stencil
+//       cotangents A_n(x) (grad c, lap c, grad T, grad p) and the site's share
+//       of dJ/dsigmaT.
+// adj_stencil_kernel forms M_0 after the last one.
+// The linearisation point (c, T, p, j of F_n) comes from a moment tape; the
+// populations themselves are read only when the relaxation times vary with c.
 //
 // The plane sets D (27 planes), M (3) and A (7, or 10 with the curvature
 // form) are row-interleaved like the state: plane p of site (x, y) in a set
 // of P planes sits at element (y P + p) nx + x (adj_index), so that a row of
 // tiles reads and writes one stretch of memory per row.
 //
-// The run is differentiated by sqrt(N) checkpointing: the forward run saves
-// every K-th state (K = ceil(sqrt N)); the backward pass replays each segment
-// from its checkpoint, writing the moment tape (and, with c-dependent
-// relaxation times, keeping the states), and sweeps it in reverse.
+// With constant relaxation times the forward run writes the moment tape of its
+// last steps itself, as many as kDirectTape holds.  What is left, and any run
+// with c-dependent relaxation times, is differentiated by sqrt(N)
+// checkpointing: the forward run saves every K-th state (K = ceil(sqrt N));
+// the backward pass replays each segment from its checkpoint, writing the
+// moment tape (and, with c-dependent relaxation times, keeping the states),
+// and sweeps it in reverse.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -59,10 +64,10 @@ __host__ __device__ __forceinline__ size_t adj_index(int P, int p, size_t nx, si
 struct AdjArgs {
   StepArgs s;          // constants; s.tape = moments of F_n, s.src = F_n (VARTAU)
   const void *d_in;    // D_{n+1}: 27 planes of R
-  const void *m_in;    // M_{n+1}: 3 planes of R (f, g, hbar groups)
+  const void *a_in;    // A_{n+1}: 7 planes of R, or 10 with the curvature form
   void *d_out;         // D_n
-  void *a;             // A_n: kAdjA planes of R (collide writes, stencil reads)
-  void *m_out;         // M_n
+  void *a_out;         // A_n
+  void *m_out;         // M_0: 3 planes of R (f, g, hbar groups), adj_stencil_kernel only
   double *part;        // [tiles] dJ/dsigmaT partials, accumulated over steps
   double *dtw;         // [2][nx] dJ/dT_wall (bottom, top), accumulated
   int ntx;             // tiles along x
@@ -262,14 +267,118 @@ __device__ __forceinline__ void site_adjoint(const StepArgs &a, const Consts<R> 
 }
 
 
-// ---- adjoint step, part 1: pull and collision transpose ----------------------
+// ---- stencil transposes ---------------------------------------------------------
+// weight of neighbour direction k in the Hessian stencil of c, applied to the
+// cotangents (a_xx, a_xy, a_yy) of the site reading it: w_k (9 xi_x^2 - 3),
+// 9 w_k xi_x xi_y and w_k (9 xi_y^2 - 3)
+template <typename R>
+__device__ __forceinline__ R hess_w(int kk, R axx, R axy, R ayy) {
+  const R wk = wq<R>(kk);
+  const R ex = R(kEx[kk]), ey = R(kEy[kk]);
+  return wk * ((R(9) * ex * ex - R(3)) * axx + R(9) * ex * ey * axy + (R(9) * ey * ey - R(3)) * ayy);
+}
+
+
+// Stencil cotangents of a tile with two sites around it.  The pitch of the
+// last tile index keeps a wave's reads of one row in consecutive banks.
+constexpr int kAdjAW = kAdjTX + 4, kAdjAH = kAdjTY + 4;
+
+// M at the cell (r, q) of such a tile: what the moments (f, g, hbar groups) of
+// the site collect from the stencils that read it; the site x = y - xi_k reads
+// y through direction k.  row: the site's row (its wall is bottom for 0, top
+// for ny - 1); wall: the cell touches one.  *tw: the wall temperature's share.
+template <typename R, bool CURV>
+__device__ __forceinline__ void adj_moments(const R (*la)[kAdjAH][kAdjAW], int r, int q,
+                                            bool wall, int dir, R inv_rcv, R *m, double *tw) {
+  R cb = 0, Tb = 0, pbv = 0;
+#pragma unroll
+  for (int kk = 1; kk < 9; ++kk) {
+    const int rr = r - kEy[kk], qq = q - kEx[kk];
+    const R wk = wq<R>(kk);
+    const R gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
+    cb += gx * la[0][rr][qq] + gy * la[1][rr][qq] + R(6) * wk * la[2][rr][qq];
+    Tb += gx * la[3][rr][qq] + gy * la[4][rr][qq];
+    pbv += gx * la[5][rr][qq] + gy * la[6][rr][qq];
+    if constexpr (CURV) cb += hess_w(kk, la[7][rr][qq], la[8][rr][qq], la[9][rr][qq]);
+  }
+  cb -= R(10.0 / 3.0) * la[2][r][q];   // centre weight of the Laplacian
+  if constexpr (CURV) cb -= R(4.0 / 3.0) * (la[7][r][q] + la[9][r][q]);   // of hxx, hyy
+  *tw = 0.0;
+  // wall rows: a site x of the same row whose stencil direction k points into
+  // the ghost row reads the mirror image of x + xi_k, which is y
+  if (wall) {
+    double twb = 0.0;
+#pragma unroll
+    for (int kk = 1; kk < 9; ++kk) {
+      if (kEy[kk] == 0 || kEy[kk] != dir) continue;
+      const int qq = q - kEx[kk];
+      const R wk = wq<R>(kk);
+      const R gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
+      cb += gx * la[0][r][qq] + gy * la[1][r][qq] + R(6) * wk * la[2][r][qq];
+      if constexpr (CURV) cb += hess_w(kk, la[7][r][qq], la[8][r][qq], la[9][r][qq]);
+      pbv += gx * la[5][r][qq] + gy * la[6][r][qq];
+      const R tg = gx * la[3][r][qq] + gy * la[4][r][qq];
+      Tb -= tg;
+      twb += 2.0 * double(tg);
+    }
+    *tw = twb;
+  }
+  m[0] = pbv;
+  m[1] = cb;
+  m[2] = Tb * inv_rcv;
+}
+
+// Loads the cotangents A of a tile and the two sites around it (zero beyond a
+// wall: no stencil there).
+template <typename R, bool CURV>
+__device__ __forceinline__ void adj_load_a(const StepArgs &a, const void *src, int x0, int y0,
+                                           int tid, R (*la)[kAdjAH][kAdjAW]) {
+  constexpr int NA = CURV ? kAdjA : 7;
+  const int nx = a.nx, ny = a.ny;
+  const bool walls = a.walls_y != 0;
+  constexpr uint32_t E = sizeof(R);
+  const uint32_t seg = (uint32_t)nx * E;   // one plane's segment of a row
+  const __amdgpu_buffer_rsrc_t ra = plane_rsrc(src, (size_t)kAdjA * nx * ny * sizeof(R));
+#pragma unroll
+  for (int e0 = 0; e0 < kAdjAH * kAdjAW; e0 += kAdjTX * kAdjTY) {
+    const int e = e0 + tid;
+    if (e >= kAdjAH * kAdjAW) break;
+    const int r = e / kAdjAW, q = e - r * kAdjAW;
+    int row = y0 - 2 + r, col = (x0 - 2 + q) % nx;
+    col = col < 0 ? col + nx : col;
+    if (walls && (row < 0 || row >= ny)) {
+#pragma unroll
+      for (int m = 0; m < NA; ++m) la[m][r][q] = R(0);
+    } else {
+      row %= ny;
+      row = row < 0 ? row + ny : row;
+      const uint32_t off = (uint32_t)row * (uint32_t)NA * seg + (uint32_t)col * E;
+#pragma unroll
+      for (int m = 0; m < NA; ++m) la[m][r][q] = buf_load<R>(ra, off, (uint32_t)m * seg);
+    }
+  }
+}
+
+// ---- one adjoint step ------------------------------------------------------------
+// Bound by memory on large grids (D in and out, A in and out, the moment tape:
+// 296 B a site in FP32) and by latency on small ones.  The stencil transposes
+// of the step before run at the head of this kernel, on the tile and the one
+// site around it whose M the pull reads, instead of in a kernel of their own:
+// one launch a step, and M makes no round trip.  Measured a step, FP32:
+// 4096 x 1024 273 + 42 us (collision transpose, then stencils) -> 279, at
+// 256 x 512 12.4 + 4.1 -> 14.1.  A kernel that recomputed A in a row-marching
+// chunk needed 180 registers and was slower than the two; this one reads the
+// A of the step before with two sites of margin.
 template <typename R, bool DEV, bool VARTAU, bool CURV>
 __global__ void __launch_bounds__(kAdjTX * kAdjTY)
-adj_collide_kernel(const AdjArgs aa) {
+adj_step_kernel(const AdjArgs aa) {
   constexpr int TW = kAdjTX + 2, TH = kAdjTY + 2;
   __shared__ double lc[TH][TW];
   __shared__ R lt[TH][TW];
   __shared__ R lp[TH][TW];
+  __shared__ R la[CURV ? kAdjA : 7][kAdjAH][kAdjAW];
+  __shared__ R lm[3][TH][TW];
+  __shared__ double ltw[2][kAdjTX];
   __shared__ double red[kAdjTX * kAdjTY / 64];
 
   const StepArgs &a = aa.s;
@@ -290,6 +399,28 @@ adj_collide_kernel(const AdjArgs aa) {
     return v < 0 ? v + ny : v;
   };
 
+  const int lx = tid & (kAdjTX - 1), ly = __builtin_amdgcn_readfirstlane(tid / kAdjTX);
+  const int x = x0 + lx, y = y0 + ly;
+  const bool bot = walls && y == 0, top = walls && y == ny - 1;
+  const uint32_t s = (uint32_t)(y * nx + x);
+  constexpr uint32_t E = sizeof(R);
+  const uint32_t seg = (uint32_t)nx * E;   // one plane's segment of a row
+  const __amdgpu_buffer_rsrc_t rd = plane_rsrc(aa.d_in, 27 * n * sizeof(R));
+  // lambda* = Stream^T lambda_{n+1}: its D part, in flight while the moments
+  // and M are formed
+  R lam[27];
+  if (x < nx && y < ny) {
+#pragma unroll
+    for (int i = 0; i < 9; ++i) {
+      const bool out = (kEy[i] < 0 && bot) || (kEy[i] > 0 && top);
+      const int dq = out ? kOpp[i] : i;
+      const int sy = out || i == 0 ? y : wrapy(y + kEy[i]), sx = out || i == 0 ? x : wrapx(x + kEx[i]);
+#pragma unroll
+      for (int lat = 0; lat < 3; ++lat)
+        lam[9 * lat + i] =
+            buf_load<R>(rd, (uint32_t)sx * E, (uint32_t)sy * 27u * seg + (uint32_t)(9 * lat + dq) * seg);
+    }
+  }
   // moments of the tile and its one-site halo; ghost rows beyond a wall
   // mirror c and p and hold T_ghost = 2 T_wall - T (deviations: 2 (T_wall -
   // Ts) - Delta T)
@@ -311,42 +442,33 @@ adj_collide_kernel(const AdjArgs aa) {
       lp[r][q] = tape_r[n + s];
     }
   }
+  adj_load_a<R, CURV>(a, aa.a_in, x0, y0, tid, la);
+  __syncthreads();
+  // M_{n+1} of the tile and the sites around it
+  const R inv_rcv = R(1.0 / a.rcv);
+  for (int e = tid; e < TH * TW; e += kAdjTX * kAdjTY) {
+    const int r = e / TW, q = e - r * TW, row = y0 - 1 + r;
+    const bool wall = walls && (row == 0 || row == ny - 1);
+    R m[3];
+    double twm;
+    adj_moments<R, CURV>(la, r + 1, q + 1, wall, row == 0 ? -1 : 1, inv_rcv, m, &twm);
+#pragma unroll
+    for (int g = 0; g < 3; ++g) lm[g][r][q] = m[g];
+    if (wall && r >= 1 && r <= kAdjTY && q >= 1 && q <= kAdjTX) ltw[row == 0 ? 0 : 1][q - 1] = twm;
+  }
   __syncthreads();
 
-  const int lx = tid & (kAdjTX - 1), ly = tid / kAdjTX;
-  const int x = x0 + lx, y = y0 + ly;
   double ds = 0.0;
   if (x < nx && y < ny) {
     const Consts<R> k(a);
-    const uint32_t s = (uint32_t)(y * nx + x);
-    constexpr uint32_t E = sizeof(R);
-    const uint32_t seg = (uint32_t)nx * E;   // one plane's segment of a row
-    const __amdgpu_buffer_rsrc_t rd = plane_rsrc(aa.d_in, 27 * n * sizeof(R));
-    const __amdgpu_buffer_rsrc_t rm = plane_rsrc(aa.m_in, 3 * n * sizeof(R));
-    auto ldD = [&](int q, int yy, int xx) {
-      return buf_load<R>(rd, (uint32_t)yy * 27u * seg + (uint32_t)xx * E, (uint32_t)q * seg);
-    };
-    auto ldM = [&](int g, int yy, int xx) {
-      return buf_load<R>(rm, (uint32_t)yy * 3u * seg + (uint32_t)xx * E, (uint32_t)g * seg);
-    };
-    // lambda* = Stream^T lambda_{n+1}
-    R lam[27];
-    const bool bot = walls && y == 0, top = walls && y == ny - 1;
     double tw_acc = 0.0;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       const bool out = (kEy[i] < 0 && bot) || (kEy[i] > 0 && top);
-      int sy = y, sx = x;
-      int dq = i;
-      if (out) {
-        dq = kOpp[i];
-      } else if (i != 0) {
-        sy = wrapy(y + kEy[i]);
-        sx = wrapx(x + kEx[i]);
-      }
-      lam[i] = ldD(dq, sy, sx) + ldM(0, sy, sx);
-      lam[9 + i] = ldD(9 + dq, sy, sx) + ldM(1, sy, sx);
-      const R lh = ldD(18 + dq, sy, sx) + ldM(2, sy, sx);
+      const int r = ly + 1 + (out ? 0 : kEy[i]), q = lx + 1 + (out ? 0 : kEx[i]);
+      lam[i] += lm[0][r][q];
+      lam[9 + i] += lm[1][r][q];
+      const R lh = lam[18 + i] + lm[2][r][q];
       if (out) {
         lam[18 + i] = -lh;
         tw_acc += 2.0 * double(wq<R>(i)) * a.rcv * double(lh);
@@ -354,7 +476,7 @@ adj_collide_kernel(const AdjArgs aa) {
         lam[18 + i] = lh;
       }
     }
-    if (bot || top) aa.dtw[(bot ? 0 : nx) + x] += tw_acc;
+    if (bot || top) aa.dtw[(bot ? 0 : nx) + x] += tw_acc + ltw[bot ? 0 : 1][lx];
     // linearisation point and stencils, as in the forward step
     const int cx = lx + 1, cy = ly + 1;
     const double cd = lc[cy][cx];
@@ -410,7 +532,7 @@ adj_collide_kernel(const AdjArgs aa) {
                                        R(gcx_d), R(gcy_d), R(lap_d), gTx, gTy, gpx, gpy,
                                        R(hxx_d), R(hxy_d), R(hyy_d), lam, db, da, &ds);
     const __amdgpu_buffer_rsrc_t wd = plane_rsrc(aa.d_out, 27 * n * sizeof(R));
-    const __amdgpu_buffer_rsrc_t wa = plane_rsrc(aa.a, kAdjA * n * sizeof(R));
+    const __amdgpu_buffer_rsrc_t wa = plane_rsrc(aa.a_out, kAdjA * n * sizeof(R));
 #pragma unroll
     for (int q = 0; q < 27; ++q)
       buf_store<R>(db[q], wd, (uint32_t)y * 27u * seg + (uint32_t)x * E, (uint32_t)q * seg);
@@ -436,113 +558,45 @@ adj_collide_kernel(const AdjArgs aa) {
   }
 }
 
-// ---- adjoint step, part 2: stencil transposes --------------------------------
-// weight of neighbour direction k in the Hessian stencil of c, applied to the
-// cotangents (a_xx, a_xy, a_yy) of the site reading it: w_k (9 xi_x^2 - 3),
-// 9 w_k xi_x xi_y and w_k (9 xi_y^2 - 3)
-template <typename R>
-__device__ __forceinline__ R hess_w(int kk, R axx, R axy, R ayy) {
-  const R wk = wq<R>(kk);
-  const R ex = R(kEx[kk]), ey = R(kEy[kk]);
-  return wk * ((R(9) * ex * ex - R(3)) * axx + R(9) * ex * ey * axy + (R(9) * ey * ey - R(3)) * ayy);
-}
-
-
+// M_0 from A_0, after the last adjoint step
 template <typename R, bool CURV>
 __global__ void __launch_bounds__(kAdjTX * kAdjTY)
 adj_stencil_kernel(const AdjArgs aa) {
-  constexpr int TW = kAdjTX + 2, TH = kAdjTY + 2;
-  constexpr int NA = CURV ? kAdjA : 7;
-  __shared__ R la[NA][TH][TW];
-
+  __shared__ R la[CURV ? kAdjA : 7][kAdjAH][kAdjAW];
   const StepArgs &a = aa.s;
   const int nx = a.nx, ny = a.ny;
-  const bool walls = a.walls_y != 0;
-  const size_t n = (size_t)nx * (size_t)ny;
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int x0 = (tile % aa.ntx) * kAdjTX, y0 = (tile / aa.ntx) * kAdjTY;
   const int tid = threadIdx.x;
-  constexpr uint32_t E = sizeof(R);
-  const uint32_t seg = (uint32_t)nx * E;   // one plane's segment of a row
-  const __amdgpu_buffer_rsrc_t ra = plane_rsrc(aa.a, kAdjA * n * sizeof(R));
-  auto wrapx = [&](int v) {
-    v %= nx;
-    return v < 0 ? v + nx : v;
-  };
-  auto wrapy = [&](int v) {
-    v %= ny;
-    return v < 0 ? v + ny : v;
-  };
-  auto ghost = [&](int row) { return walls && (row < 0 || row >= ny); };
-  for (int e = tid; e < TH * TW; e += kAdjTX * kAdjTY) {
-    const int r = e / TW, q = e - r * TW;
-    const int row = y0 - 1 + r;
-    if (ghost(row)) {
-#pragma unroll
-      for (int m = 0; m < NA; ++m) la[m][r][q] = R(0);   // no stencil at a ghost site
-    } else {
-      const uint32_t off = (uint32_t)wrapy(row) * (uint32_t)NA * seg + (uint32_t)wrapx(x0 - 1 + q) * E;
-#pragma unroll
-      for (int m = 0; m < NA; ++m) la[m][r][q] = buf_load<R>(ra, off, (uint32_t)m * seg);
-    }
-  }
+  adj_load_a<R, CURV>(a, aa.a_in, x0, y0, tid, la);
   __syncthreads();
   const int lx = tid & (kAdjTX - 1), ly = tid / kAdjTX;
   const int x = x0 + lx, y = y0 + ly;
   if (x >= nx || y >= ny) return;
-  const int cx = lx + 1, cy = ly + 1;
-  R cb = 0, Tb = 0, pbv = 0;
-  // site x = y - xi_k reads y through direction k of its stencil
+  const bool wall = a.walls_y != 0 && (y == 0 || y == ny - 1);
+  R m[3];
+  double tw;
+  adj_moments<R, CURV>(la, ly + 2, lx + 2, wall, y == 0 ? -1 : 1, R(1.0 / a.rcv), m, &tw);
+  if (wall) aa.dtw[(y == 0 ? 0 : nx) + x] += tw;
+  const uint32_t seg = (uint32_t)(nx * sizeof(R));
+  const uint32_t off = (uint32_t)y * 3u * seg + (uint32_t)(x * sizeof(R));
+  const __amdgpu_buffer_rsrc_t wm = plane_rsrc(aa.m_out, 3 * (size_t)nx * ny * sizeof(R));
 #pragma unroll
-  for (int kk = 1; kk < 9; ++kk) {
-    const int r = cy - kEy[kk], q = cx - kEx[kk];
-    const R wk = wq<R>(kk);
-    const R gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
-    cb += gx * la[0][r][q] + gy * la[1][r][q] + R(6) * wk * la[2][r][q];
-    Tb += gx * la[3][r][q] + gy * la[4][r][q];
-    pbv += gx * la[5][r][q] + gy * la[6][r][q];
-    if constexpr (CURV) cb += hess_w(kk, la[7][r][q], la[8][r][q], la[9][r][q]);
-  }
-  cb -= R(10.0 / 3.0) * la[2][cy][cx];   // centre weight of the Laplacian
-  if constexpr (CURV) cb -= R(4.0 / 3.0) * (la[7][cy][cx] + la[9][cy][cx]);   // of hxx, hyy
-  // wall rows: a site x of the same row whose stencil direction k points into
-  // the ghost row reads the mirror image of x + xi_k, which is y
-  if (walls && (y == 0 || y == ny - 1)) {
-    const int dir = y == 0 ? -1 : 1;
-    double twb = 0.0;
-#pragma unroll
-    for (int kk = 1; kk < 9; ++kk) {
-      if (kEy[kk] != dir) continue;
-      const int q = cx - kEx[kk];
-      const R wk = wq<R>(kk);
-      const R gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
-      cb += gx * la[0][cy][q] + gy * la[1][cy][q] + R(6) * wk * la[2][cy][q];
-      if constexpr (CURV) cb += hess_w(kk, la[7][cy][q], la[8][cy][q], la[9][cy][q]);
-      pbv += gx * la[5][cy][q] + gy * la[6][cy][q];
-      const R tg = gx * la[3][cy][q] + gy * la[4][cy][q];
-      Tb -= tg;
-      twb += 2.0 * double(tg);
-    }
-    aa.dtw[(y == 0 ? 0 : nx) + x] += twb;
-  }
-  const uint32_t off = (uint32_t)y * 3u * seg + (uint32_t)x * E;
-  const __amdgpu_buffer_rsrc_t wm = plane_rsrc(aa.m_out, 3 * n * sizeof(R));
-  buf_store<R>(pbv, wm, off, 0u);
-  buf_store<R>(cb, wm, off, seg);
-  buf_store<R>(Tb * R(1.0 / a.rcv), wm, off, 2 * seg);
+  for (int g = 0; g < 3; ++g) buf_store<R>(m[g], wm, off, (uint32_t)g * seg);
 }
 
-// lambda_N from the seed on c = sum_q g_q: D = the seed on each g_q, M = 0.
+// lambda_N from the seed on c = sum_q g_q: D = the seed on each g_q, and M = 0
+// through stencil cotangents A = 0 (na planes).
 template <typename R>
 __global__ void __launch_bounds__(256)
-adj_seed_kernel(R *__restrict__ d, R *__restrict__ m, const double *__restrict__ dJdc,
+adj_seed_kernel(R *__restrict__ d, R *__restrict__ a, int na, const double *__restrict__ dJdc,
                 size_t n, size_t nx) {
   const size_t s = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int q = blockIdx.y;
   if (s >= n) return;
   const size_t y = s / nx, x = s - y * nx;
   d[adj_index(27, q, nx, y, x)] = (q >= 9 && q < 18) ? R(dJdc[s]) : R(0);
-  if (q < 3) m[adj_index(3, q, nx, y, x)] = R(0);
+  if (q < na) a[adj_index(na, q, nx, y, x)] = R(0);
 }
 
 // lambda_0 = D_0 + M_0 -> FP64 outputs: dJ/dF_0 (optional) and dJ/dT_0 through

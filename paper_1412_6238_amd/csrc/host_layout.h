@@ -98,12 +98,23 @@ struct AdjLayout {
   size_t off_tape2;       // a second tape, 2 states and K moment sets: with
                           // constant relaxation times the replay of the next
                           // segment fills it while the adjoint steps read the first
-  size_t off_lam;         // D x2 (27 planes), M x2 (3 planes), A (kAdjA planes)
+  size_t off_lam;         // D x2 (27 planes), M_0 (3 planes of 6), A (kAdjA planes)
   size_t off_part;        // per-block FP64 partial sums of dJ/dsigmaT
   size_t off_tw;          // FP64 [2][nx] dJ/dTwall accumulators
   size_t off_out;         // FP64 scalar result
+  size_t off_direct;      // moment sets that the recorded run writes itself
+  int64_t direct;         // ... of this many last steps
+  size_t off_a2;          // a second set of stencil cotangents
   size_t total;
 };
+// Bytes of moment sets that a recorded run writes as it goes, instead of
+// leaving them to a replay in the backward pass: 16 GiB of the 288 GB, all of
+// 5,400 steps of 256 x 512 in FP32 or the last 170 of 4096 x 1024.  Taping
+// costs the forward step 24 bytes a site; the replay costs the whole step
+// again.  Measured, forward and backward of 40 steps of 4096 x 1024 and of 200
+// of 256 x 512, with the one-kernel adjoint step: 27.1 -> 17.8 ms and
+// 6.4 -> 4.9 ms.
+constexpr size_t kDirectTape = size_t(16) << 30;
 
 inline int64_t adj_segment_length(int64_t nsteps) {
   if (nsteps <= 1) return 1;
@@ -117,7 +128,7 @@ inline int adj_tiles_x(int nx) { return (nx + kAdjTX - 1) / kAdjTX; }
 inline int adj_tiles_y(int ny) { return (ny + kAdjTY - 1) / kAdjTY; }
 
 inline AdjLayout adj_layout(int nx, int ny, size_t state_bytes, size_t value_bytes,
-                            int64_t record_steps) {
+                            int64_t record_steps, bool direct) {
   AdjLayout A{};
   auto al = [](size_t v) { return (v + 255) / 256 * 256; };
   A.record_steps = record_steps;
@@ -136,6 +147,11 @@ inline AdjLayout adj_layout(int nx, int ny, size_t state_bytes, size_t value_byt
   A.off_part = o; o += al((size_t)adj_tiles_x(nx) * adj_tiles_y(ny) * sizeof(double));
   A.off_tw = o; o += al(2 * (size_t)nx * sizeof(double));
   A.off_out = o; o += 256;
+  A.direct = direct ? std::min<int64_t>(record_steps, (int64_t)(kDirectTape / A.mom_bytes)) : 0;
+  if (const char *e = std::getenv("LBE_CSF_DIRECT"))   // at most this many steps
+    A.direct = std::min<int64_t>(A.direct, std::max(0, std::atoi(e)));
+  A.off_direct = o; o += (size_t)A.direct * A.mom_bytes;
+  A.off_a2 = o; o += kAdjA * A.plane_bytes;
   A.total = o;
   return A;
 }
@@ -384,15 +400,20 @@ inline Layout make_layout(const lbe_csf_params *p, int64_t record_steps) {
   L.off_tw = o; o = align_up(o + 2 * (size_t)p->nx * 8);
   // diagnostic partials: one per block of the row-marching or the tile kernel,
   // or per wave of the two-step kernel
+  // (sized alike with two densities, whose steps never pair)
+  lbe_csf_params one = *p;
+  one.rho2 = 0.0;
   const size_t nparts = (size_t)std::max({la.nblocks, tile_blocks(p->nx, p->ny),
-                                          pair_launch(p, L.state_bytes).nparts});
+                                          pair_launch(&one, L.state_bytes).nparts});
   L.off_part = o; o = align_up(o + nparts * kNumPartials * 8);
   L.off_ring = o; o = align_up(o + (size_t)kDiagRing * sizeof(DiagRecord));
   L.off_cnt = o; o = align_up(o + 4 * sizeof(int64_t));
   L.off_rec = o; o = align_up(o + sizeof(DiagRecord));
   L.off_pc = o; o = align_up(o + (two_densities(p) ? n * 8 : 0));   // pressure of Eq. 9
   L.off_adj = o;
-  L.adj = adj_layout(p->nx, p->ny, L.state_bytes, vb, record_steps);
+  // constant relaxation times need the moments only, so these can be taped
+  const bool constant = p->tau_f[0] == p->tau_f[1] && p->tau_T[0] == p->tau_T[1];
+  L.adj = adj_layout(p->nx, p->ny, L.state_bytes, vb, record_steps, constant);
   o = align_up(o + L.adj.total);
   L.total = o;
   return L;

@@ -90,6 +90,7 @@ struct StepArgs {
   // then T, p, jx, jy in the arithmetic type (T and p as deviations in the
   // FP32 form), each a plane of nx*ny
   void *tape;
+  void *tape2;              // two steps per launch: the tape of the state in between
 };
 
 template <typename R>

@@ -58,6 +58,7 @@ struct lbe_csf {
   // record of the last recorded run
   bool recorded;
   int64_t rec_start, rec_steps, rec_K;
+  int64_t rec_direct;   // first segment whose moments the run taped itself
   std::string err;
   StepArgs base;      // constants filled once
   int device;         // the HIP device current at creation
@@ -387,11 +388,14 @@ int launch_small(lbe_csf *h, int64_t nsteps) {
 }
 
 template <typename R, bool DEV, int FORM, int NW>
-void launch_pair_as(const lbe_csf *h, const StepArgs &a, bool diag) {
+void launch_pair_as(const lbe_csf *h, const StepArgs &a, bool diag, bool tape) {
   constexpr int M = kStore | FORM, T = DEV ? kStream : 0;
   const int nb = h->pair.nblocks, nt = 64 * NW;
   hipStream_t st = h->stream;
-  if (DEV && h->la.stream) {
+  if (tape) {
+    if (DEV && h->la.stream) pair_step_kernel<R, R, DEV, M | T | kTape, NW><<<nb, nt, 0, st>>>(a);
+    else pair_step_kernel<R, R, DEV, M | kTape, NW><<<nb, nt, 0, st>>>(a);
+  } else if (DEV && h->la.stream) {
     if (diag) pair_step_kernel<R, R, DEV, M | T | kDiag, NW><<<nb, nt, 0, st>>>(a);
     else pair_step_kernel<R, R, DEV, M | T, NW><<<nb, nt, 0, st>>>(a);
   } else {
@@ -401,23 +405,26 @@ void launch_pair_as(const lbe_csf *h, const StepArgs &a, bool diag) {
 }
 
 template <typename R, bool DEV, int FORM, int TY>
-void launch_pair_tile(const lbe_csf *h, const StepArgs &a, bool diag) {
+void launch_pair_tile(const lbe_csf *h, const StepArgs &a, bool diag, bool tape) {
   constexpr int M = kStore | FORM, nt = 64 * (TY + 2 * kPairHalo);
   const int nb = h->pair.nblocks;
-  if (diag) pair_tile_kernel<R, R, DEV, M | kDiag, TY><<<nb, nt, 0, h->stream>>>(a);
+  if (tape) pair_tile_kernel<R, R, DEV, M | kTape, TY><<<nb, nt, 0, h->stream>>>(a);
+  else if (diag) pair_tile_kernel<R, R, DEV, M | kDiag, TY><<<nb, nt, 0, h->stream>>>(a);
   else pair_tile_kernel<R, R, DEV, M, TY><<<nb, nt, 0, h->stream>>>(a);
 }
 template <typename R, bool DEV, int FORM>
-void launch_pair_tiles(const lbe_csf *h, const StepArgs &a, bool diag) {
-  if (h->pair.tile == 2) launch_pair_tile<R, DEV, FORM, 2>(h, a, diag);
-  else if (DEV && h->pair.tile == 8) launch_pair_tile<R, DEV, FORM, (DEV ? 8 : 4)>(h, a, diag);
-  else launch_pair_tile<R, DEV, FORM, 4>(h, a, diag);
+void launch_pair_tiles(const lbe_csf *h, const StepArgs &a, bool diag, bool tape) {
+  if (h->pair.tile == 2) launch_pair_tile<R, DEV, FORM, 2>(h, a, diag, tape);
+  else if (DEV && h->pair.tile == 8) launch_pair_tile<R, DEV, FORM, (DEV ? 8 : 4)>(h, a, diag, tape);
+  else launch_pair_tile<R, DEV, FORM, 4>(h, a, diag, tape);
 }
 
-// Two plain steps in one launch, the first with diagnostics where asked; the
-// state alternates once.
-int launch_pair(lbe_csf *h, bool diag) {
+// Two plain steps in one launch, the first with diagnostics where asked, or
+// both with their moments taped; the state alternates once.
+int launch_pair(lbe_csf *h, bool diag, void *tape = nullptr, void *tape2 = nullptr) {
   StepArgs a = h->base;
+  a.tape = tape;
+  a.tape2 = tape2;
   a.src = h->state[h->cur];
   a.dst = h->state[1 - h->cur];
   a.nstrips = h->pair.nstrips;
@@ -425,18 +432,18 @@ int launch_pair(lbe_csf *h, bool diag) {
   const bool f64 = h->P.precision == LBE_CSF_FP64, curv = h->P.csf_form == 1;
   const bool wide = h->pair.nw > 2;
   if (h->pair.tile > 0) {
-    if (f64 && curv) launch_pair_tiles<double, false, kCurv>(h, a, diag);
-    else if (f64) launch_pair_tiles<double, false, 0>(h, a, diag);
-    else if (curv) launch_pair_tiles<float, true, kCurv>(h, a, diag);
-    else launch_pair_tiles<float, true, 0>(h, a, diag);
-  } else if (f64 && curv && wide) launch_pair_as<double, false, kCurv, 4>(h, a, diag);
-  else if (f64 && curv) launch_pair_as<double, false, kCurv, 2>(h, a, diag);
-  else if (f64 && wide) launch_pair_as<double, false, 0, 4>(h, a, diag);
-  else if (f64) launch_pair_as<double, false, 0, 2>(h, a, diag);
-  else if (curv && wide) launch_pair_as<float, true, kCurv, 8>(h, a, diag);
-  else if (curv) launch_pair_as<float, true, kCurv, 1>(h, a, diag);
-  else if (wide) launch_pair_as<float, true, 0, 8>(h, a, diag);
-  else launch_pair_as<float, true, 0, 1>(h, a, diag);
+    if (f64 && curv) launch_pair_tiles<double, false, kCurv>(h, a, diag, tape != nullptr);
+    else if (f64) launch_pair_tiles<double, false, 0>(h, a, diag, tape != nullptr);
+    else if (curv) launch_pair_tiles<float, true, kCurv>(h, a, diag, tape != nullptr);
+    else launch_pair_tiles<float, true, 0>(h, a, diag, tape != nullptr);
+  } else if (f64 && curv && wide) launch_pair_as<double, false, kCurv, 4>(h, a, diag, tape != nullptr);
+  else if (f64 && curv) launch_pair_as<double, false, kCurv, 2>(h, a, diag, tape != nullptr);
+  else if (f64 && wide) launch_pair_as<double, false, 0, 4>(h, a, diag, tape != nullptr);
+  else if (f64) launch_pair_as<double, false, 0, 2>(h, a, diag, tape != nullptr);
+  else if (curv && wide) launch_pair_as<float, true, kCurv, 8>(h, a, diag, tape != nullptr);
+  else if (curv) launch_pair_as<float, true, kCurv, 1>(h, a, diag, tape != nullptr);
+  else if (wide) launch_pair_as<float, true, 0, 8>(h, a, diag, tape != nullptr);
+  else launch_pair_as<float, true, 0, 1>(h, a, diag, tape != nullptr);
   HIPCHK(h, hipGetLastError());
   h->cur = 1 - h->cur;
   h->step += 2;
@@ -454,12 +461,11 @@ int launch_reduce(lbe_csf *h, int64_t step, bool append, int nparts) {
   return LBE_CSF_OK;
 }
 
-// One adjoint step: collision transpose, then stencil transpose.
+// One adjoint step.
 template <typename R, bool DEV, bool CURV>
 void launch_adj(bool vartau, const AdjArgs &aa, int nblocks, hipStream_t st) {
-  if (vartau) adj_collide_kernel<R, DEV, true, CURV><<<nblocks, kAdjTX * kAdjTY, 0, st>>>(aa);
-  else adj_collide_kernel<R, DEV, false, CURV><<<nblocks, kAdjTX * kAdjTY, 0, st>>>(aa);
-  adj_stencil_kernel<R, CURV><<<nblocks, kAdjTX * kAdjTY, 0, st>>>(aa);
+  if (vartau) adj_step_kernel<R, DEV, true, CURV><<<nblocks, kAdjTX * kAdjTY, 0, st>>>(aa);
+  else adj_step_kernel<R, DEV, false, CURV><<<nblocks, kAdjTX * kAdjTY, 0, st>>>(aa);
 }
 
 // Reverse sweep over the recorded run: for each segment, last first, replay
@@ -477,8 +483,10 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
   char *lam = base + A.off_lam;
   const size_t pl = A.plane_bytes;
   void *D[2] = {lam, lam + 27 * pl};
-  void *M[2] = {lam + 54 * pl, lam + 57 * pl};
-  void *Abuf = lam + 60 * pl;
+  void *M0 = lam + 54 * pl;
+  void *Abuf[2] = {lam + 60 * pl, base + A.off_a2};
+  const bool curv = h->P.csf_form == 1;
+  const int na = curv ? kAdjA : 7;
   double *part = reinterpret_cast<double *>(base + A.off_part);
   double *tw = reinterpret_cast<double *>(base + A.off_tw);
   double *outv = reinterpret_cast<double *>(base + A.off_out);
@@ -488,11 +496,11 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
   const dim3 g27((unsigned)((n + 255) / 256), 27);
   if (f64)
     adj_seed_kernel<double><<<g27, 256, 0, st>>>(static_cast<double *>(D[0]),
-                                                 static_cast<double *>(M[0]), dJdc, n,
+                                                 static_cast<double *>(Abuf[0]), na, dJdc, n,
                                                  (size_t)nx);
   else
     adj_seed_kernel<float><<<g27, 256, 0, st>>>(static_cast<float *>(D[0]),
-                                                static_cast<float *>(M[0]), dJdc, n,
+                                                static_cast<float *>(Abuf[0]), na, dJdc, n,
                                                 (size_t)nx);
   HIPCHK(h, hipGetLastError());
   int cur = 0;
@@ -502,7 +510,7 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
   const bool vartau = h->base.dtauf != 0.0 || h->base.dtauT != 0.0;
   AdjArgs aa;
   aa.s = h->base;
-  aa.a = Abuf;
+  aa.m_out = M0;
   aa.part = part;
   aa.dtw = tw;
   aa.ntx = ntx;
@@ -514,7 +522,9 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
   // the adjoint steps of segment k read the other (events order the reuse).
   char *tape_base[2] = {base + A.off_tape, base + A.off_tape2};
   const size_t tape_states[2] = {(size_t)A.K, 2};
-  const bool overlap = !vartau && nseg > 1;
+  // segments from kd on were taped by the run itself; the rest are replayed
+  const int64_t kd = vartau ? nseg : h->rec_direct;
+  const bool overlap = !vartau && kd > 0;
   hipEvent_t ev_start = nullptr, ev_rep[2] = {nullptr, nullptr}, ev_adj[2] = {nullptr, nullptr};
   // the events are released on every way out of this function
   struct EventSet {
@@ -546,7 +556,8 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
     if (j == 0) return chk0 + (size_t)k * A.state_bytes;
     return tape_base[b] + (size_t)(vartau ? j : (j & 1)) * A.state_bytes;
   };
-  auto moments = [&](int b, int64_t j) -> void * {
+  auto moments = [&](int64_t k, int b, int64_t j) -> void * {
+    if (k >= kd) return base + A.off_direct + (size_t)((k - kd) * K + j) * A.mom_bytes;
     return tape_base[b] + tape_states[b] * A.state_bytes + (size_t)j * A.mom_bytes;
   };
   // the forward steps of segment k from its checkpoint, writing the moment
@@ -557,13 +568,13 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
       const bool last = j + 1 == m;   // its successor is not needed
       const int rc = launch_step_on(h, on, last ? kTape : (kStore | kTape), state(k, b, j),
                                     last ? nullptr : state(k, b, j + 1), nullptr, nullptr,
-                                    nullptr, nullptr, nullptr, moments(b, j));
+                                    nullptr, nullptr, nullptr, moments(k, b, j));
       if (rc != LBE_CSF_OK) return rc;
     }
     return (int)LBE_CSF_OK;
   };
   auto tape_of = [&](int64_t k) { return overlap ? (int)(k & 1) : 0; };
-  if (overlap) {
+  if (overlap && kd == nseg) {
     const int rc = replay(nseg - 1, tape_of(nseg - 1), st);
     if (rc != LBE_CSF_OK) return rc;
   }
@@ -571,31 +582,30 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
     const int64_t m = seg_len(k);
     const int b = tape_of(k);
     if (overlap) {
-      if (k > 0) {
+      if (k > 0 && k - 1 < kd) {
         // segment k - 1 into the other tape, once the adjoint steps of
         // segment k + 1 (which read that tape) are done
         const int bn = tape_of(k - 1);
-        hipError_t e = hipStreamWaitEvent(h->aux, k + 1 < nseg ? ev_adj[bn] : ev_start, 0);
+        hipError_t e = hipStreamWaitEvent(h->aux, k + 1 < kd ? ev_adj[bn] : ev_start, 0);
         int rc = e == hipSuccess ? replay(k - 1, bn, h->aux) : (int)LBE_CSF_EDEVICE;
         if (rc == LBE_CSF_OK && hipEventRecord(ev_rep[bn], h->aux) != hipSuccess)
           rc = LBE_CSF_EDEVICE;
         if (rc != LBE_CSF_OK)
           return rc == LBE_CSF_EDEVICE ? fail(h, rc, "backward: second stream") : rc;
       }
-      if (k < nseg - 1 && hipStreamWaitEvent(st, ev_rep[b], 0) != hipSuccess)
+      if (k < kd && k < nseg - 1 && hipStreamWaitEvent(st, ev_rep[b], 0) != hipSuccess)
         return fail(h, LBE_CSF_EDEVICE, "backward: stream wait");
-    } else {
+    } else if (k < kd) {
       const int rc = replay(k, b, st);
       if (rc != LBE_CSF_OK) return rc;
     }
     for (int64_t j = m - 1; j >= 0; --j) {
       aa.s.src = vartau ? state(k, b, j) : nullptr;
-      aa.s.tape = moments(b, j);
+      aa.s.tape = moments(k, b, j);
       aa.d_in = D[cur];
-      aa.m_in = M[cur];
+      aa.a_in = Abuf[cur];
       aa.d_out = D[1 - cur];
-      aa.m_out = M[1 - cur];
-      const bool curv = h->P.csf_form == 1;
+      aa.a_out = Abuf[1 - cur];
       if (f64) {
         if (curv) launch_adj<double, false, true>(vartau, aa, nb, st);
         else launch_adj<double, false, false>(vartau, aa, nb, st);
@@ -607,19 +617,25 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
         return fail(h, LBE_CSF_EDEVICE, "backward: adjoint kernel launch");
       cur = 1 - cur;
     }
-    if (overlap && hipEventRecord(ev_adj[b], st) != hipSuccess) {
+    if (overlap && k < kd && hipEventRecord(ev_adj[b], st) != hipSuccess) {
       return fail(h, LBE_CSF_EDEVICE, "backward: event record");
     }
   }
+  // the stencil transposes of the last step
+  aa.a_in = Abuf[cur];
+  if (f64 && curv) adj_stencil_kernel<double, true><<<nb, kAdjTX * kAdjTY, 0, st>>>(aa);
+  else if (f64) adj_stencil_kernel<double, false><<<nb, kAdjTX * kAdjTY, 0, st>>>(aa);
+  else if (curv) adj_stencil_kernel<float, true><<<nb, kAdjTX * kAdjTY, 0, st>>>(aa);
+  else adj_stencil_kernel<float, false><<<nb, kAdjTX * kAdjTY, 0, st>>>(aa);
   const unsigned g1 = (unsigned)((n + 255) / 256);
   if (dF0 || dT0) {
     if (f64)
       adj_finish_kernel<double><<<g1, 256, 0, st>>>(static_cast<const double *>(D[cur]),
-                                                    static_cast<const double *>(M[cur]), dF0,
+                                                    static_cast<const double *>(M0), dF0,
                                                     dT0, n, (size_t)nx, h->base.rcv);
     else
       adj_finish_kernel<float><<<g1, 256, 0, st>>>(static_cast<const float *>(D[cur]),
-                                                   static_cast<const float *>(M[cur]), dF0,
+                                                   static_cast<const float *>(M0), dF0,
                                                    dT0, n, (size_t)nx, h->base.rcv);
   }
   adj_sum_kernel<<<1, 256, 0, st>>>(part, nb, outv);
@@ -823,6 +839,20 @@ int lbe_csf_step(lbe_csf *h, int64_t nsteps, int32_t record) {
     h->rec_steps = nsteps;
     h->rec_K = K;
   }
+  // the last segments of a record that fit the direct tape write their moments
+  // as they run and need no checkpoint: from step d0 on
+  int64_t d0 = nsteps;
+  if (record) {
+    const int64_t nseg = (nsteps + K - 1) / K;
+    int64_t k = nseg;
+    while (k > 0 && nsteps - (k - 1) * K <= h->L.adj.direct) --k;
+    h->rec_direct = k;
+    d0 = std::min(nsteps, k * K);
+  }
+  auto direct_tape = [&](int64_t s) -> void * {
+    return s >= d0 ? h->ws + h->L.off_adj + h->L.adj.off_direct + (size_t)(s - d0) * h->L.adj.mom_bytes
+                   : nullptr;
+  };
   const int de = h->P.diag_every;
   bool any_diag = false;
   for (int64_t s = 0; s < nsteps; ++s) {
@@ -837,7 +867,7 @@ int lbe_csf_step(lbe_csf *h, int64_t nsteps, int32_t record) {
         continue;
       }
     }
-    if (record && s % K == 0) {
+    if (record && s < d0 && s % K == 0) {
       // checkpoint F_{start + s}
       const int rc = adj_save_checkpoint(h->ws + h->L.off_adj, h->L.adj, s / K,
                                          h->state[h->cur], h->L.state_bytes, h->stream);
@@ -845,10 +875,10 @@ int lbe_csf_step(lbe_csf *h, int64_t nsteps, int32_t record) {
     }
     const bool diag = de > 0 && (h->step % de == 0);
     // two steps at once: the second neither carries diagnostics nor starts
-    // from a checkpoint
-    if (h->pair.rows > 0 && s + 1 < nsteps && !(de > 0 && (h->step + 1) % de == 0) &&
-        !(record && (s + 1) % K == 0)) {
-      int rc = launch_pair(h, diag);
+    // from a checkpoint, and both or neither are taped
+    const bool mixed = record && ((s < d0 && (s + 1) % K == 0) || (s >= d0 && diag));
+    if (h->pair.rows > 0 && s + 1 < nsteps && !(de > 0 && (h->step + 1) % de == 0) && !mixed) {
+      int rc = launch_pair(h, diag, direct_tape(s), direct_tape(s + 1));
       if (rc == LBE_CSF_OK && diag) {
         rc = launch_reduce(h, h->step - 2, true, h->pair.nparts);
         any_diag = true;
@@ -857,8 +887,15 @@ int lbe_csf_step(lbe_csf *h, int64_t nsteps, int32_t record) {
       ++s;
       continue;
     }
-    int rc = launch_step(h, diag ? (kStore | kDiag) : kStore, h->state[h->cur],
-                         h->state[1 - h->cur], nullptr, nullptr, nullptr, nullptr, nullptr);
+    void *tape = direct_tape(s);
+    int rc = LBE_CSF_OK;
+    if (tape && diag)   // a diagnostic step tapes in a launch of its own
+      rc = launch_step(h, kTape, h->state[h->cur], nullptr, nullptr, nullptr, nullptr, nullptr,
+                       nullptr, tape);
+    if (rc == LBE_CSF_OK)
+      rc = launch_step(h, diag ? (kStore | kDiag) : (tape ? (kStore | kTape) : kStore),
+                       h->state[h->cur], h->state[1 - h->cur], nullptr, nullptr, nullptr, nullptr,
+                       nullptr, diag ? nullptr : tape);
     if (rc != LBE_CSF_OK) return rc;
     if (diag) {
       rc = launch_reduce(h, h->step, true, h->diag_blocks);

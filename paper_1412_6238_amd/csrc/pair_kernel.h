@@ -63,6 +63,33 @@ __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_wave_barrier();
 }
 
+// A lane or row that has nothing to store carries an offset past the end of
+// the buffer, whose stores the hardware drops (the host keeps states below
+// host::kPairMaxBytes, so the offset is past the end of any of them).
+constexpr uint32_t kDropped = 0xfffffff0u;
+static_assert(host::kPairMaxBytes <= kDropped);
+
+// The moment tape of a wave's row (kTape): only its own sites are written.
+template <typename R>
+struct PairTape {
+  __amdgpu_buffer_rsrc_t rd;
+  uint32_t n, row, vc, vr;   // sites; first site of the row; lane offsets in the c and R planes
+  __device__ __forceinline__ PairTape(void *tape, uint32_t n_, uint32_t row_, int x, bool own)
+      : n(n_), row(row_) {
+    rd = plane_rsrc(tape, (size_t)n_ * (8 + 4 * sizeof(R)));
+    vc = own ? (uint32_t)x * 8u : kDropped;
+    vr = own ? (uint32_t)x * (uint32_t)sizeof(R) : kDropped;
+  }
+  __device__ __forceinline__ void write(double c, R T, R p, R jx, R jy) const {
+    constexpr uint32_t E = sizeof(R);
+    buf_store<double>(c, rd, vc, row * 8u);
+    buf_store<R>(T, rd, vr, n * 8u + row * E);
+    buf_store<R>(p, rd, vr, n * (8u + E) + row * E);
+    buf_store<R>(jx, rd, vr, n * (8u + 2u * E) + row * E);
+    buf_store<R>(jy, rd, vr, n * (8u + 3u * E) + row * E);
+  }
+};
+
 // F_{n+1} of one row into LDS and registers
 template <typename S, typename R, bool EDGE>
 struct PairMidSink {
@@ -70,6 +97,8 @@ struct PairMidSink {
   int lane;              // index of the lane's own column in the LDS rows
   int su, sprev, sm;     // slots of this row's and (bottom wall) the row before's up values, of mid
   bool bot, top;
+  const PairTape<R> *tp;
+  __device__ __forceinline__ void tape(double c, R T, R p, R jx, R jy) const { tp->write(c, T, p, jx, jy); }
   __device__ __forceinline__ static constexpr int up_of(int i) { return i == 2 ? 0 : (i == 5 ? 1 : 2); }
   template <typename V>
   __device__ __forceinline__ void operator()(int i, int lat, V v) const {
@@ -100,13 +129,7 @@ struct PairMidSink {
   }
 };
 
-// F_{n+2}: only the wave's own columns and the chunk's own rows are stored; a
-// lane or row that has none carries an offset past the end of the buffer,
-// whose stores the hardware drops (the host keeps states below host::kPairMaxBytes,
-// so the offset is past the end of any of them).
-constexpr uint32_t kDropped = 0xfffffff0u;
-static_assert(host::kPairMaxBytes <= kDropped);
-
+// F_{n+2}: only the wave's own columns and the chunk's own rows are stored.
 struct PairOut {
   __amdgpu_buffer_rsrc_t rd;
   uint32_t pb, own, up, down, rb0, rb1;
@@ -118,6 +141,8 @@ struct PairOut {
 template <typename S, bool STREAM, bool EDGE, bool WALL>
 struct PairOutSink {
   const PairOut &o;
+  const PairTape<S> *tp;
+  __device__ __forceinline__ void tape(double c, S T, S p, S jx, S jy) const { tp->write(c, T, p, jx, jy); }
   template <typename V>
   __device__ __forceinline__ void operator()(int i, int lat, V v) const {
     const bool out = WALL && ((kEy[i] > 0 && o.top) || (kEy[i] < 0 && o.bot));
@@ -146,7 +171,7 @@ struct PairOutSink {
 template <typename S, typename R, bool DEV, int MODE, int NW>
 __global__ void __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 1 : 2, sizeof(S) == 8 ? 1 : 2)))
 pair_step_kernel(const StepArgs a) {
-  static_assert((MODE & ~(kStream | kCurv | kDiag)) == kStore, "pairs of plain steps");
+  static_assert((MODE & ~(kStream | kCurv | kDiag | kTape)) == kStore, "pairs of steps");
   constexpr bool STREAM = (MODE & kStream) != 0;
   constexpr int kMode = MODE & ~(kStream | kDiag), kMode1 = MODE & ~kStream;
   __shared__ PairLds<S, R> lds[NW];
@@ -259,12 +284,14 @@ pair_step_kernel(const StepArgs a) {
       else put(0, r + 1, nxt);
       wave_lds_fence();
       const int sS = slot(r - 1), sC = slot(r), sN = slot(r + 1);
+      const PairTape<R> tape(a.tape, (uint32_t)n, (uint32_t)(wrap_row(r) * nx), x,
+                             owned && r >= y0 && r < y1);
       const bool bot = EDGE && walls && r == 0, top = EDGE && walls && r == ny - 1;
       site_collide<R, DEV, kMode1, EDGE, false>(
           a, wrap_row(r), x, bot, top, &l.c[0][sS][lane], &l.c[0][sC][lane], &l.c[0][sN][lane],
           &l.t[0][sS][lane], &l.t[0][sC][lane], &l.t[0][sN][lane], &l.p[0][sS][lane],
           &l.p[0][sC][lane], &l.p[0][sN][lane], cur, acc,
-          PairMidSink<S, R, EDGE>{l, k, sC, sS, r & 1, bot, top});
+          PairMidSink<S, R, EDGE>{l, k, sC, sS, r & 1, bot, top, &tape});
       if constexpr ((MODE & kDiag) != 0) {
 #pragma unroll
         for (int m = 0; m < kNumPartials; ++m) {
@@ -310,6 +337,8 @@ pair_step_kernel(const StepArgs a) {
       const int sS = slot(j - 1), sC = slot(j), sN = slot(j + 1);
       const bool bot = EDGE && walls && j == 0, top = EDGE && walls && j == ny - 1;
       const int jw = EDGE ? wrap_row(j) : j;
+      const PairTape<R> tape(a.tape2, (uint32_t)n, (uint32_t)(jw * nx), x,
+                             owned && j >= y0 && j < y1);
       PairOut out;
       out.rd = plane_rsrc(a.dst, state_bytes_for<S>(n));
       out.pb = opaque(pb);
@@ -343,7 +372,7 @@ pair_step_kernel(const StepArgs a) {
           a, jw, x, bot, top, &l.c[1][sS][lane], &l.c[1][sC][lane], &l.c[1][sN][lane],
           &l.t[1][sS][lane], &l.t[1][sC][lane], &l.t[1][sN][lane], &l.p[1][sS][lane],
           &l.p[1][sC][lane], &l.p[1][sN][lane], f1, acc,
-          PairOutSink<S, STREAM, EDGE, EDGE>{out});
+          PairOutSink<S, STREAM, EDGE, EDGE>{out, &tape});
     }
   };
   // two rows per turn, so that the rows in registers change roles by name;
@@ -409,6 +438,8 @@ struct PairTileSink {
   int k, row;            // own column in the LDS rows, row of the block
   bool bot, top;
   RowVals<R> &f1;        // receives the rest populations
+  const PairTape<R> *tp;
+  __device__ __forceinline__ void tape(double c, R T, R p, R jx, R jy) const { tp->write(c, T, p, jx, jy); }
   template <typename V>
   __device__ __forceinline__ void operator()(int i, int lat, V v) const {
     if (i == 0) {
@@ -429,7 +460,7 @@ struct PairTileSink {
 template <typename S, typename R, bool DEV, int MODE, int TY>
 __global__ void __launch_bounds__(64 * (TY + 2 * kPairHalo))
 pair_tile_kernel(const StepArgs a) {
-  static_assert((MODE & ~(kCurv | kDiag)) == kStore, "pairs of plain steps");
+  static_assert((MODE & ~(kCurv | kDiag | kTape)) == kStore, "pairs of steps");
   constexpr int H = TY + 2 * kPairHalo;
   constexpr int kMode = MODE & ~kDiag;
   __shared__ PairTileLds<S, R, TY> l;
@@ -501,11 +532,12 @@ pair_tile_kernel(const StepArgs a) {
   __syncthreads();
   if (live && row >= 1 && row < H - 1) {
     RowVals<R> f1;
+    const PairTape<R> tape(a.tape, (uint32_t)n, (uint32_t)(jr * nx), x, owned);
     constexpr std::integral_constant<int, MODE> mode{};
     if (sizeof(S) == 8 || bot || top)
-      collide(mode, std::true_type{}, PairTileSink<S, R, TY, true>{l, k, row, bot, top, f1});
+      collide(mode, std::true_type{}, PairTileSink<S, R, TY, true>{l, k, row, bot, top, f1, &tape});
     else
-      collide(mode, std::false_type{}, PairTileSink<S, R, TY, false>{l, k, row, bot, top, f1});
+      collide(mode, std::false_type{}, PairTileSink<S, R, TY, false>{l, k, row, bot, top, f1, &tape});
     cur.v[0] = f1.v[0];
     cur.g0r = f1.g0r;
     cur.h0r = f1.h0r;
@@ -549,11 +581,12 @@ pair_tile_kernel(const StepArgs a) {
     }
     out.x0 = owned ? (uint32_t)x * (uint32_t)sizeof(T0) : kDropped;
     out.x1 = owned ? (uint32_t)x * (uint32_t)sizeof(T1) : kDropped;
+    const PairTape<R> tape(a.tape2, (uint32_t)n, (uint32_t)(jr * nx), x, owned);
     constexpr std::integral_constant<int, kMode> mode{};
     if (sizeof(S) == 8 || bot || top)
-      collide(mode, std::true_type{}, PairOutSink<S, false, true, true>{out});
+      collide(mode, std::true_type{}, PairOutSink<S, false, true, true>{out, &tape});
     else
-      collide(mode, std::false_type{}, PairOutSink<S, false, true, false>{out});
+      collide(mode, std::false_type{}, PairOutSink<S, false, true, false>{out, &tape});
   }
 }
 

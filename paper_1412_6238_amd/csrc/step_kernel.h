@@ -197,7 +197,7 @@ __device__ __forceinline__ R relax(R v, R w, R eq, R om) {
 // Moments, stencils, closures and collision of site (x, j), with its
 // diagnostics and field output.  With kStore the post-collision values go to
 // sink(i, lattice, value) as they are formed, so that their stores spread over
-// the collision, and the two rest populations to sink.rest(g0, h0).  The
+// the collision, and the two rest populations to sink.rest(g0, h0); with kTape the moments go to sink.tape.  The
 // directions come pair by pair, or with BYDIR in their order 1, 2, 3, ...,
 // which holds two pairs at a time: the row-marching FP32 step on 4096^2 stores
 // 2.5% faster that way (737 against 756 us), the two-step kernel has no
@@ -226,7 +226,6 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
 #pragma clang fp contract(off)
   constexpr bool VR = (MODE & kVarRho) != 0;
   const SiteConsts<R> &k = site_consts<R>(a);
-  const size_t n = (size_t)a.nx * (size_t)a.ny;
   // order parameter and its stencils in FP64
   const double cd = cC[1];
   double gcx, gcy, mu, tHt = 0.0;
@@ -277,16 +276,7 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
   for (int q = 0; q < 9; ++q) fv[q] = double(cur.v[q]);
   const double m5 = fv[5] - fv[7], m6 = fv[6] - fv[8];
   const double jx = (fv[1] - fv[3]) + (m5 - m6), jy = (fv[2] - fv[4]) + (m5 + m6);
-  if (MODE & kTape) {
-    const size_t s = (size_t)j * a.nx + x;
-    double *tc = static_cast<double *>(a.tape);
-    R *tr = reinterpret_cast<R *>(tc + n);
-    tc[s] = cd;
-    tr[s] = Tv;
-    tr[n + s] = pv;
-    tr[2 * n + s] = R(jx);
-    tr[3 * n + s] = R(jy);
-  }
+  if constexpr ((MODE & kTape) != 0) sink.tape(cd, Tv, pv, R(jx), R(jy));
   // closures: sigma = sigma0 - sigmaT (T - Tref)
   const double sigma = fma_(-a.sigmaT, double(Tv) + (Trow - a.Tref), a.sigma0);
   // capillary part along grad c: kcap sigma mu (potential form) or
@@ -523,6 +513,8 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
 // direction at the site itself.
 template <typename S, bool STREAM>
 struct RowSink {
+  void *tp;                      // moment tape, and this site in it
+  size_t ts, tn;
   __amdgpu_buffer_rsrc_t rd;
   uint32_t pb;                   // a plane's segment of a row
   uint32_t own, up, down;        // row offsets
@@ -534,6 +526,9 @@ struct RowSink {
       : x(x_), bot(bot_), top(top_) {
     const size_t n = (size_t)a.nx * (size_t)a.ny;
     const uint32_t RB = (uint32_t)row_bytes<S>(a.nx);
+    tp = a.tape;
+    ts = (size_t)j * a.nx + x;
+    tn = n;
     // one descriptor for the whole destination state (below 4 GiB)
     rd = plane_rsrc(a.dst, state_bytes_for<S>(n));
     pb = (uint32_t)(a.nx * sizeof(S));
@@ -557,6 +552,16 @@ struct RowSink {
       buf_store_stream<S>(S(v), rd, vo, so);
     else
       buf_store<S>(S(v), rd, vo, so);
+  }
+  template <typename R>
+  __device__ __forceinline__ void tape(double c, R T, R p, R jx, R jy) const {
+    double *tc = static_cast<double *>(tp);
+    R *tr = reinterpret_cast<R *>(tc + tn);
+    tc[ts] = c;
+    tr[ts] = T;
+    tr[tn + ts] = p;
+    tr[2 * tn + ts] = jx;
+    tr[3 * tn + ts] = jy;
   }
   __device__ __forceinline__ void rest(double g0, double h0) const {
     rest_store<S, 0, STREAM>(g0, rd, 0u, x, own + rb0);

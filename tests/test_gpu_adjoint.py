@@ -331,3 +331,30 @@ def test_adjoint_droplet_full(lbe, precision, tol, tol_wall):
     rd, rc = _vec_rel(ad_d, fd_d), _vec_rel(ad_c, fd_c)
     _say(f"  {len(ad_d)} directions: relative 2-norm {rd:.2e}; {len(ad_c)} components: {rc:.2e}")
     assert rd <= tol_wall and rc <= tol_wall
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("nx,ny,direct,diag", [(64, 40, 0, 0), (64, 40, 5, 0), (64, 40, 23, 4),
+                                               (300, 200, 9, 0), (300, 200, 23, 0)])
+def test_direct_tape_does_not_matter(lbe, monkeypatch, nx, ny, direct, diag, precision):
+    """A recorded run whose last steps write their moments as they run (none,
+    part of a segment's worth, two segments, all; diagnostic steps among them;
+    pairs of steps in tiles and single steps) gives the gradients of a run
+    whose every segment is replayed: the same tape and the same adjoint
+    kernel, so bitwise in FP64; FP32 likewise, the forward kernels giving the
+    same bits."""
+    import torch
+    case = wl.random_case(nx, ny, seed=nx + direct, walls_y=1, n_drops=2)
+    p = dict(case["params"], tau_f=(0.8, 0.8), tau_T=(0.7, 0.7))
+    seed_field = torch.as_tensor(np.random.default_rng(5).standard_normal((ny, nx)))
+    out = []
+    for steps in ("0", str(direct)):
+        monkeypatch.setenv("LBE_CSF_DIRECT", steps)
+        print(f"case direct tape {steps} of 23 steps {nx}x{ny} {precision}", flush=True)
+        sim = lbe.Simulation(p, case["phi0"], case["T0"], case["Twall_bot"], case["Twall_top"],
+                             precision=precision, record_steps=23, diag_every=diag)
+        sim.step(23, record=True)
+        out.append(sim.backward(seed_field, want_F0=True, want_T0=True))
+    assert out[0]["sigmaT"] == out[1]["sigmaT"]
+    for k in ("Twall", "F0", "T0"):
+        np.testing.assert_array_equal(out[1][k].cpu().numpy(), out[0][k].cpu().numpy())
