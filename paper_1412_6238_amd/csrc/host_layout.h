@@ -342,6 +342,35 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
   return L;
 }
 
+// Steps with two densities in one launch (density_step_kernel): strips and
+// chunks of one wave each; rows = 0 where they take two launches.
+constexpr int kDensityHalo = 3;
+inline PairLaunch density_launch(const lbe_csf_params *p, size_t state_bytes) {
+  PairLaunch L{0, 0, 0, 0, 0, 0};
+  const bool fp32 = p->precision == LBE_CSF_FP32_DEV;
+  const char *e = std::getenv("LBE_CSF_PAIR");
+  const bool forced = e && std::atoi(e) > 0;
+  if (p->ny < 8 || state_bytes > kPairMaxBytes || (e && !forced)) return L;
+  for (const char *v : {"LBE_CSF_NW", "LBE_CSF_ROWS", "LBE_CSF_PIPE", "LBE_CSF_STREAM",
+                        "LBE_CSF_TILE", "LBE_CSF_SMALL"})
+    if (!forced && std::getenv(v)) return L;
+  const size_t n = (size_t)p->nx * p->ny;
+  if (!forced && n < (size_t)(fp32 ? 700000 : 500000)) return L;
+  constexpr int cols = 64 - 2 * kDensityHalo;
+  L.nw = n > 3000000 ? (fp32 ? 8 : 4) : 1;
+  const int ngroups = ((p->nx + cols - 1) / cols + L.nw - 1) / L.nw;
+  const int wx = std::max(4, (p->nx + ngroups * L.nw - 1) / (ngroups * L.nw));
+  L.nstrips = (p->nx + wx - 1) / wx;
+  const int chunks = std::max(1, kNumCUs * (fp32 ? 8 : 4) / L.nw / ngroups);
+  L.rows = (p->ny + chunks - 1) / chunks;
+  if (const char *r = std::getenv("LBE_CSF_PAIR_ROWS"))
+    L.rows = std::max(1, std::min(p->ny, std::atoi(r)));
+  const int nchunks = (p->ny + L.rows - 1) / L.rows;
+  L.nblocks = ngroups * nchunks;
+  L.nparts = L.nstrips * nchunks;
+  return L;
+}
+
 struct Layout {
   size_t state_bytes;
   size_t off_a, off_b, off_tw, off_part, off_ring, off_cnt, off_rec, off_pc, off_adj, total;
@@ -400,11 +429,12 @@ inline Layout make_layout(const lbe_csf_params *p, int64_t record_steps) {
   L.off_tw = o; o = align_up(o + 2 * (size_t)p->nx * 8);
   // diagnostic partials: one per block of the row-marching or the tile kernel,
   // or per wave of the two-step kernel
-  // (sized alike with two densities, whose steps never pair)
+  // (sized alike with one density and two)
   lbe_csf_params one = *p;
   one.rho2 = 0.0;
   const size_t nparts = (size_t)std::max({la.nblocks, tile_blocks(p->nx, p->ny),
-                                          pair_launch(&one, L.state_bytes).nparts});
+                                          pair_launch(&one, L.state_bytes).nparts,
+                                          density_launch(&one, L.state_bytes).nparts});
   L.off_part = o; o = align_up(o + nparts * kNumPartials * 8);
   L.off_ring = o; o = align_up(o + (size_t)kDiagRing * sizeof(DiagRecord));
   L.off_cnt = o; o = align_up(o + 4 * sizeof(int64_t));

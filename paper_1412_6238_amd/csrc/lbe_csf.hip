@@ -28,6 +28,7 @@
 #include "../../include/lbe_csf.h"
 #include "adjoint.h"
 #include "aux_kernels.h"
+#include "density_kernel.h"
 #include "pair_kernel.h"
 #include "step_kernel.h"
 
@@ -63,6 +64,7 @@ struct lbe_csf {
   StepArgs base;      // constants filled once
   int device;         // the HIP device current at creation
   PairLaunch pair;    // two plain steps per launch where pair.rows > 0 (pair_step_kernel)
+  PairLaunch density;   // steps with two densities in one launch where rows > 0
   bool tile;          // steps in tiles (tile_step_kernel; latency-bound grids)
   int diag_blocks;    // diagnostic partials per launch (blocks of the step kernel used)
   size_t small_lds;   // > 0: plain steps run many per launch (small grids)
@@ -332,6 +334,38 @@ int launch_step_on(lbe_csf *h, hipStream_t stream, int mode, const void *src, vo
   }
   if (!launch_any(h->P.precision == LBE_CSF_FP64, mode, h->la, a, stream))
     return fail(h, LBE_CSF_EINVAL, "no step kernel for mode " + std::to_string(mode));
+  HIPCHK(h, hipGetLastError());
+  return LBE_CSF_OK;
+}
+
+// One step with two densities in one launch.
+int launch_density(lbe_csf *h, bool diag) {
+  StepArgs a = h->base;
+  a.src = h->state[h->cur];
+  a.dst = h->state[1 - h->cur];
+  a.nstrips = h->density.nstrips;
+  a.rows_per_chunk = h->density.rows;
+  const bool f64 = h->P.precision == LBE_CSF_FP64, curv = h->P.csf_form == 1;
+  const int nb = h->density.nblocks;
+  hipStream_t st = h->stream;
+  constexpr int V = kStore | kVarRho;
+  auto go = [&](auto form, auto waves) {
+    constexpr int F = decltype(form)::value, W = decltype(waves)::value;
+    constexpr int W64 = W > 4 ? 4 : W;
+    if (f64 && diag)
+      density_step_kernel<double, double, false, V | F | kDiag, W64><<<nb, 64 * W64, 0, st>>>(a);
+    else if (f64) density_step_kernel<double, double, false, V | F, W64><<<nb, 64 * W64, 0, st>>>(a);
+    else if (diag) density_step_kernel<float, float, true, V | F | kDiag, W><<<nb, 64 * W, 0, st>>>(a);
+    else density_step_kernel<float, float, true, V | F, W><<<nb, 64 * W, 0, st>>>(a);
+  };
+  constexpr std::integral_constant<int, kCurv> curvature{};
+  constexpr std::integral_constant<int, 0> potential{};
+  constexpr std::integral_constant<int, 1> one{};
+  constexpr std::integral_constant<int, 8> wide{};
+  if (curv && h->density.nw > 1) go(curvature, wide);
+  else if (curv) go(curvature, one);
+  else if (h->density.nw > 1) go(potential, wide);
+  else go(potential, one);
   HIPCHK(h, hipGetLastError());
   return LBE_CSF_OK;
 }
@@ -733,6 +767,7 @@ int lbe_csf_create(const lbe_csf_params *params, void *workspace, size_t bytes,
   h->L = L;
   h->la = launch_for(params, L.state_bytes);
   h->pair = pair_launch(params, L.state_bytes);
+  h->density = two_densities(params) ? density_launch(params, L.state_bytes) : PairLaunch{};
   h->small_lds = 0;
   h->small_res = false;
   h->tile = use_tile_kernel(params);
@@ -892,13 +927,16 @@ int lbe_csf_step(lbe_csf *h, int64_t nsteps, int32_t record) {
     if (tape && diag)   // a diagnostic step tapes in a launch of its own
       rc = launch_step(h, kTape, h->state[h->cur], nullptr, nullptr, nullptr, nullptr, nullptr,
                        nullptr, tape);
-    if (rc == LBE_CSF_OK)
+    if (rc == LBE_CSF_OK && h->density.rows > 0)
+      rc = launch_density(h, diag);
+    else if (rc == LBE_CSF_OK)
       rc = launch_step(h, diag ? (kStore | kDiag) : (tape ? (kStore | kTape) : kStore),
                        h->state[h->cur], h->state[1 - h->cur], nullptr, nullptr, nullptr, nullptr,
                        nullptr, diag ? nullptr : tape);
     if (rc != LBE_CSF_OK) return rc;
     if (diag) {
-      rc = launch_reduce(h, h->step, true, h->diag_blocks);
+      rc = launch_reduce(h, h->step, true,
+                         h->density.rows > 0 ? h->density.nparts : h->diag_blocks);
       if (rc != LBE_CSF_OK) return rc;
       any_diag = true;
     }

@@ -292,9 +292,9 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
   // u = (3 j + F / 2) / rho
   const double uxd = fma_(0.5, Fx, 3.0 * jx) * inv_rho, uyd = fma_(0.5, Fy, 3.0 * jy) * inv_rho;
   const double grx = VR ? a.drho * gcx : 0.0, gry = VR ? a.drho * gcy : 0.0;
-  if (MODE & kPress) {
+  if constexpr ((MODE & kPress) != 0) {
     // the pressure of Eq. 9: p = sum f + (1/2) u.grad(rho cs^2)
-    a.pc_out[(size_t)j * a.nx + x] = fma_(0.5 / 3.0, fma_(uxd, grx, uyd * gry), double(pv));
+    sink.pressure(fma_(0.5 / 3.0, fma_(uxd, grx, uyd * gry), double(pv)));
     return;
   }
   if (MODE & kDiag) {
@@ -514,6 +514,7 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
 template <typename S, bool STREAM>
 struct RowSink {
   void *tp;                      // moment tape, and this site in it
+  double *pc;                    // kPress: the pressure plane
   size_t ts, tn;
   __amdgpu_buffer_rsrc_t rd;
   uint32_t pb;                   // a plane's segment of a row
@@ -527,6 +528,7 @@ struct RowSink {
     const size_t n = (size_t)a.nx * (size_t)a.ny;
     const uint32_t RB = (uint32_t)row_bytes<S>(a.nx);
     tp = a.tape;
+    pc = a.pc_out;
     ts = (size_t)j * a.nx + x;
     tn = n;
     // one descriptor for the whole destination state (below 4 GiB)
@@ -553,6 +555,7 @@ struct RowSink {
     else
       buf_store<S>(S(v), rd, vo, so);
   }
+  __device__ __forceinline__ void pressure(double v) const { pc[ts] = v; }
   template <typename R>
   __device__ __forceinline__ void tape(double c, R T, R p, R jx, R jy) const {
     double *tc = static_cast<double *>(tp);

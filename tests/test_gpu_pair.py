@@ -63,3 +63,37 @@ def test_pair_matches_single_steps(lbe, monkeypatch, kind, nx, ny, walls, rows, 
         for k in ("mass", "energy", "sum_cy", "sum_cx"):
             assert a[k] == pytest.approx(b[k], rel=1e-11), k
     sys.stdout.flush()
+
+
+# strips of 58 columns and chunks of few rows: as above, for the step with two
+# densities, whose cones are one row and column narrower
+DENSITY = [(3, 8, 1, 1), (7, 9, 0, 4), (58, 12, 1, 5), (59, 13, 1, 3), (117, 16, 0, 7),
+           (200, 31, 1, 4), (130, 40, 1, 40), (300, 25, 0, 12)]
+
+
+@pytest.mark.parametrize("nx,ny,walls,rows", DENSITY)
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("precision", ["fp64", "fp32_dev"])
+def test_one_launch_density_step_matches_two(lbe, monkeypatch, nx, ny, walls, rows, form, precision):
+    """Two densities in one launch (density_step_kernel) against the pressure
+    pass and the step: the states bitwise the same, the diagnostics to
+    rounding."""
+    case = wl.random_case(nx, ny, seed=7 * nx + ny, walls_y=walls, n_drops=2, csf_form=form,
+                          rho2=2.5)
+    out = []
+    for pair in ("0", "1"):
+        monkeypatch.setenv("LBE_CSF_PAIR", pair)
+        monkeypatch.setenv("LBE_CSF_PAIR_ROWS", str(rows))
+        print(f"case one launch={pair} {nx}x{ny} walls={walls} rows={rows} form={form} {precision}",
+              flush=True)
+        sim = lbe.Simulation(case["params"], case["phi0"], case["T0"],
+                             case["Twall_bot"] if walls else None,
+                             case["Twall_top"] if walls else None, precision=precision,
+                             diag_every=3)
+        sim.step(5)
+        out.append((sim.get_state().cpu().numpy(), sim.diag_history()))
+    np.testing.assert_array_equal(out[1][0], out[0][0])
+    assert len(out[0][1]) == len(out[1][1]) == 2
+    for a, b in zip(out[0][1], out[1][1]):
+        for k in ("mass", "energy", "sum_cy", "sum_cx"):
+            assert a[k] == pytest.approx(b[k], rel=1e-11), k
