@@ -25,12 +25,19 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
-# algorithmic bytes per site update: the 27 distributions read once and
+# algorithmic bytes per pass over a site: the 27 distributions read once and
 # written once, 4 bytes each in the FP32 form (216) and 8 in FP64 (432)
 BYTES_PER_SITE = {"fp32_dev": 216, "fp64": 432}
-# bytes the state layout actually moves per site update: the FP32 form keeps
+# bytes the state layout actually moves per pass: the FP32 form keeps
 # the rest population g_0 in FP64, 2 x (26 x 4 + 8) = 224
 STORED_BYTES_PER_SITE = {"fp32_dev": 224, "fp64": 432}
+# steps that one pass over the state takes: two in one launch on grids whose
+# state does not stay in the caches (pair_launch in host_layout.h), so a step
+# reads and writes half of the above
+PAIRED_SITES = {"fp32_dev": 1_100_000, "fp64": 500_000}
+# two densities: the state is read once from these sizes on (density_launch),
+# and half again by a pressure pass below
+ONE_LAUNCH_SITES = {"fp32_dev": 700_000, "fp64": 500_000}
 REPEATS = 5
 # the step kernel and its launch shape and store policy (host_layout.h)
 KERNEL_SOURCES = ("paper_1412_6238_amd/csrc/step_kernel.h", "paper_1412_6238_amd/csrc/pair_kernel.h",
@@ -56,7 +63,7 @@ def kernel_hash():
 
 
 def traffic_from_profile(workload, precision, sites, csf_form=0):
-    """Measured HBM bytes per launch from the committed counter summary, if it
+    """Measured HBM bytes per step from the committed counter summary, if it
     was taken on the current kernel source (else None)."""
     form = "_curvature" if csf_form == 1 else ""
     path = os.path.join(ROOT, "profiles", f"traffic_step_{workload}_{precision}{form}.json")
@@ -65,7 +72,7 @@ def traffic_from_profile(workload, precision, sites, csf_form=0):
     d = json.load(open(path))
     if d.get("kernel_hash") != kernel_hash():
         return None
-    return d.get("bytes_per_launch")
+    return d["bytes_per_launch"] / d.get("steps_per_launch", 1)   # of one step
 
 
 def _oracle_band_mlups(w, rows, seconds, threads=None):
@@ -299,17 +306,22 @@ def main():
         mass_drift = d_last["mass"] / hist[0]["mass"] - 1.0
     diag_in_windows = len([h for h in hist if h["step"] >= args.warmup])
 
-    # dominant kernel: the fused step, one launch per step; its average
-    # launch time is the window time over the steps (the window also holds
-    # one small reduction launch per diagnostic step)
+    # dominant kernel: the fused step; the window also holds one small
+    # reduction launch per diagnostic step
     bps = BYTES_PER_SITE[args.precision]
     stored = STORED_BYTES_PER_SITE[args.precision]
+    per_pass = 1
     if args.rho2 > 0:
-        # two densities: the pressure pass reads the 27 values (half the
-        # step's bytes) and writes the FP64 pressure of Eq. 9 (8 B), which
-        # the step then reads (8 B)
-        bps += bps // 2 + 8 + 8
-        stored += stored // 2 + 8 + 8
+        if sites < ONE_LAUNCH_SITES[args.precision]:
+            # two launches: the pressure pass reads the 27 values (half the
+            # step's bytes) and writes the FP64 pressure of Eq. 9 (8 B), which
+            # the step then reads (8 B)
+            bps += bps // 2 + 8 + 8
+            stored += stored // 2 + 8 + 8
+    elif sites >= PAIRED_SITES[args.precision]:
+        per_pass = 2
+        bps //= 2
+        stored //= 2
     achieved = bps * sites / (ms_per_step / 1e3) / 1e9
     traffic = (traffic_from_profile(args.workload, args.precision, sites, args.csf_form)
                if args.rho2 <= 0 else None)
@@ -330,7 +342,8 @@ def main():
                    "sites": sites, "diag_every": args.diag_every,
                    "capillary_form": "curvature" if args.csf_form == 1 else "potential",
                    "densities": [p["rho"], args.rho2] if args.rho2 > 0 else [p["rho"]],
-                   "bytes_per_site_update": bps, "stored_bytes_per_site_update": stored},
+                   "bytes_per_site_update": bps, "stored_bytes_per_site_update": stored,
+                   "steps_per_pass": per_pass},
         "roofline": {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBS,
                      "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBS, 4),
                      "traffic": traffic},

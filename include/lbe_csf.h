@@ -137,7 +137,9 @@ typedef struct lbe_csf lbe_csf; /* opaque host object */
 
 /* Bytes of device workspace needed for these parameters.  record_steps > 0
  * reserves room for lbe_csf_backward after a recorded run of that many steps
- * (ceil(sqrt(N)) spaced checkpoints plus one segment of replay states).
+ * (ceil(sqrt(N)) spaced checkpoints plus one segment of replay states and,
+ * with constant relaxation times, the moments that the run tapes itself, up to
+ * 48 GiB while the total stays within 64 GiB).
  * Two densities add one FP64 plane of nx*ny (the pressure of Eq. 9).
  * Errors: EINVAL for invalid parameters or NULL bytes. */
 LBE_CSF_API int lbe_csf_workspace_size(const lbe_csf_params *params, int64_t record_steps,
@@ -162,8 +164,9 @@ LBE_CSF_API int lbe_csf_create(const lbe_csf_params *params, void *workspace, si
  * this run for lbe_csf_backward (the run must start at the handle's current
  * state and N = nsteps <= record_steps; the adjoint covers both force
  * forms with one density, so record = 1 is EINVAL with two densities);
- * record = 0 discards any record.  With two densities every
- * step is two launches: the pressure of Eq. 9, then the step.
+ * record = 0 discards any record.  With two densities a step is two launches,
+ * the pressure of Eq. 9 and then the step, or one on large grids; with one
+ * density a launch may take two steps.
  * With diag_every > 0 the diagnostics of F_n for every n divisible by
  * diag_every in [start, start + nsteps) are computed inside the step kernel
  * and this call synchronises once at its end to check them: ENONFINITE if any
@@ -209,7 +212,8 @@ LBE_CSF_API int64_t lbe_csf_step_count(const lbe_csf *h);
 
 /* Gradient of J = sum_x c_N(x) dJdc(x) (for the centroid objective
  * dJdc = (y - J)/sum c) through the recorded run of N steps (Sec. II-III step
- * transposed), by reverse sweeps over checkpoint segments with recomputation.
+ * transposed), by reverse sweeps over the moments that the run taped, or over
+ * checkpoint segments with recomputation.
  * dJ_dc: device FP64 nx*ny seed on c of the final state F_N.
  * dJ_dsigmaT: host FP64 scalar (output).
  * dJ_dTwall: device FP64 2*nx (output: bottom then top wall), through the wall

@@ -108,13 +108,15 @@ struct AdjLayout {
   size_t total;
 };
 // Bytes of moment sets that a recorded run writes as it goes, instead of
-// leaving them to a replay in the backward pass: 16 GiB of the 288 GB, all of
-// 5,400 steps of 256 x 512 in FP32 or the last 170 of 4096 x 1024.  Taping
-// costs the forward step 24 bytes a site; the replay costs the whole step
-// again.  Measured, forward and backward of 40 steps of 4096 x 1024 and of 200
-// of 256 x 512, with the one-kernel adjoint step: 27.1 -> 17.8 ms and
-// 6.4 -> 4.9 ms.
-constexpr size_t kDirectTape = size_t(16) << 30;
+// leaving them to a replay in the backward pass: at most 48 GiB of the 288 GB,
+// and only what keeps the adjoint region within 64 GiB (a record that needs
+// more than that without them is laid out as if there were none).  That is all
+// of 4,000 steps of 256 x 512 in FP32 (12.6 GB) and most of 400 steps of
+// 4096 x 1024.  Taping costs the forward step 24 bytes a site, the replay costs
+// the whole step again.  Measured, forward and backward of 40 steps of
+// 4096 x 1024 and of 200 of 256 x 512, with the one-kernel adjoint step:
+// 27.1 -> 17.8 ms and 6.4 -> 4.9 ms.
+constexpr size_t kDirectTape = size_t(48) << 30, kDirectTotal = size_t(64) << 30;
 
 inline int64_t adj_segment_length(int64_t nsteps) {
   if (nsteps <= 1) return 1;
@@ -147,7 +149,8 @@ inline AdjLayout adj_layout(int nx, int ny, size_t state_bytes, size_t value_byt
   A.off_part = o; o += al((size_t)adj_tiles_x(nx) * adj_tiles_y(ny) * sizeof(double));
   A.off_tw = o; o += al(2 * (size_t)nx * sizeof(double));
   A.off_out = o; o += 256;
-  A.direct = direct ? std::min<int64_t>(record_steps, (int64_t)(kDirectTape / A.mom_bytes)) : 0;
+  const size_t room = o < kDirectTotal ? std::min(kDirectTape, kDirectTotal - o) : 0;
+  A.direct = direct ? std::min<int64_t>(record_steps, (int64_t)(room / A.mom_bytes)) : 0;
   if (const char *e = std::getenv("LBE_CSF_DIRECT"))   // at most this many steps
     A.direct = std::min<int64_t>(A.direct, std::max(0, std::atoi(e)));
   A.off_direct = o; o += (size_t)A.direct * A.mom_bytes;
@@ -343,7 +346,15 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
 }
 
 // Steps with two densities in one launch (density_step_kernel): strips and
-// chunks of one wave each; rows = 0 where they take two launches.
+// chunks of one wave each; rows = 0 where they take two launches.  Taken from
+// 700k sites in FP32 and 500k in FP64.  Measured on MI355X, two launches ->
+// one, us per step, FP32: 4096^2 1313 -> 799, 2048^2 318 -> 215, 1500^2
+// 201 -> 146, 1030 x 777 49.0 -> 46.0, below the line 800^2 40.9 -> 40.5,
+// 512 x 1024 33.4 -> 36.1; FP64: 4096^2 2185 -> 1424, 1500^2 350 -> 226,
+// 1030 x 777 112 -> 85, 512 x 1024 57 -> 50, below it 320 x 600 24.2 -> 27.5
+// (ten rows of latency for chunks of four).  Above 3M sites neighbouring strips
+// march in step in one block, as in pair_launch: 4096^2 FP64 1791 with one wave
+// a block, 1424 with four; FP32 1126 and 799 with eight.
 constexpr int kDensityHalo = 3;
 inline PairLaunch density_launch(const lbe_csf_params *p, size_t state_bytes) {
   PairLaunch L{0, 0, 0, 0, 0, 0};

@@ -27,6 +27,9 @@
 // own site (coalesced, aligned) and pushes post-collision values to the
 // neighbours' slots in the other buffer (shifted by at most one element).
 //
+// Plain steps go two per launch where pair_kernel.h has a kernel for the grid;
+// the kernels here take the single ones.
+//
 // Work decomposition: a block owns a strip of 64*NW columns and marches up a
 // chunk of rows, one column per lane.  The moments a row's stencils need
 // (c, T, p) sit in an LDS ring of four rows, filled one row ahead of the row
@@ -878,7 +881,7 @@ step_kernel(const StepArgs a) {
 // the moments of its sites, a barrier, every lane collides and pushes its
 // sites into the other state (through L2: the two states of such a grid
 // stay in cache), a barrier.  The site arithmetic is site_moments and
-// site_update of the per-step kernel, and the halo and ghost values are
+// site_collide of the per-step kernel, and the halo and ghost values are
 // formed exactly as its ring does, so the states are bitwise the same.
 // One density; no diagnostics, fields or tape (the host runs the steps that
 // need them through step_kernel).  All waves of a block share one CU and its
