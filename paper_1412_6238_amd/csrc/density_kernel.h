@@ -14,8 +14,7 @@ namespace lbe {
 // own sites.  At row r it loads row r + 2, forms the moments of row r + 1, the
 // pressure of row r and the collision of row r - 1; the loads come before the
 // collision's stores, which they would otherwise wait for.  Four rows stay in
-// registers, so a CU holds four waves in FP64 and eight in the FP32 form.  The
-// arithmetic is that of the two launches (site_moments, site_collide with
+// registers, so a CU holds four waves.  The arithmetic is that of the two launches (site_moments, site_collide with
 // kPress and with kStore), so the states are bitwise the same.
 using host::kDensityHalo;
 
@@ -38,7 +37,7 @@ struct PressureSink {
 
 template <typename S, typename R, bool DEV, int MODE, int NW>
 __global__ void __launch_bounds__(64 * NW)
-__attribute__((amdgpu_waves_per_eu(sizeof(S) == 8 ? 1 : 2, sizeof(S) == 8 ? 1 : 2)))
+__attribute__((amdgpu_waves_per_eu(1, 1)))
 density_step_kernel(const StepArgs a) {
   static_assert((MODE & ~(kCurv | kDiag)) == (kStore | kVarRho), "steps with two densities");
   __shared__ DensityLds<R> lds[NW];
@@ -139,7 +138,7 @@ density_step_kernel(const StepArgs a) {
       wave_lds_fence();
       const int sS = slot(r - 1), sC = slot(r), sN = slot(r + 1);
       R p = 0;
-      site_collide<R, DEV, kVarRho | kPress | (MODE & kCurv), false, false>(
+      site_collide<R, DEV, kVarRho | kPress | (MODE & kCurv), false>(
           a, wrap_row(r), x, false, false, &l.c[sS][lane], &l.c[sC][lane], &l.c[sN][lane],
           &l.t[sS][lane], &l.t[sC][lane], &l.t[sN][lane], &l.sf[lane], &l.sf[lane], &l.sf[lane], B,
           acc, PressureSink<R>{p});
@@ -174,7 +173,7 @@ density_step_kernel(const StepArgs a) {
       out.rb1 = rb1;
       out.bot = bot;
       out.top = top;
-      site_collide<R, DEV, MODE, true, false>(
+      site_collide<R, DEV, MODE, true>(
           a, jw, x, bot, top, &l.c[sS][lane], &l.c[sC][lane], &l.c[sN][lane], &l.t[sS][lane],
           &l.t[sC][lane], &l.t[sN][lane], &l.p[sS][lane], &l.p[sC][lane], &l.p[sN][lane], A, acc,
           PairOutSink<S, false, true, true>{out, nullptr});

@@ -262,33 +262,35 @@ inline bool two_densities(const lbe_csf_params *p) { return p->rho2 > 0.0 && p->
 // of rows, one wave each; rows = 0 where the steps go one by one.
 //
 // Taken where a state no longer fits the caches, or close to it: FP32 from
-// 1.1M sites, FP64 from half a million (one density).  Measured on MI355X
+// 1.2M sites, FP64 from half a million (one density).  Measured on MI355X
 // against one launch per step, interleaved windows, us per step, FP32: 4096^2
-// 735 -> 417, 4096 x 1024 181 -> 118, 1500^2 116 -> 77, 1200^2 80 -> 52, and
-// below the line 1024^2 36.3 -> 36.9, 1030 x 777 28.4 -> 32.8, 512 x 1024
-// 19.9 -> 27.8; FP64: 4096^2 1385 -> 720, 2048^2 360 -> 195, 1030 x 777
-// 80 -> 51, 800^2 62 -> 40, 512 x 1024 37 -> 33, below it 600^2 27.3 -> 26.6.
-// (The chunks of a small grid are short against the eight rows that their
-// cones add.)
+// 690 -> 456, 4096 x 1024 182 -> 131, 1500^2 116 -> 84, 1200^2 80 -> 59,
+// 1200 x 1020 62 -> 52, and below the line, where two states (224 B a site)
+// still fit the 256 MB last-level cache, 1160 x 1020 40 -> 49, 1024^2 35 -> 44,
+// 512 x 1024 20 -> 34; FP64: 4096^2 1380 -> 698, 2048^2 358 -> 198, 1030 x 777
+// 80 -> 55, 800^2 60 -> 43, at the line 512 x 1024 35.4 -> 35.5, below it
+// 256 x 512 11.5 -> 23.  (The chunks of a small grid are short against the eight
+// rows that their cones add.)
 //
 // A block's waves take neighbouring strips and march in step, so that the
-// lines at their seams are read and written by one CU at one time: on 4096^2
-// eight FP32 waves a block took 406 us, four 463, two 471, one 557; four FP64
-// waves 702, two 729, one 893 (HBM bytes 1.5 times the state with one).  On
-// smaller grids that fit blocks less evenly fewer waves are as fast or
-// faster: 1200^2 FP32 53.2 with one against 55.4 with eight, FP64 82.3 with
-// two against 86.0 with four.  One block more than are resident at once would
-// run alone, so the chunks are as many as fit (FP32 eight waves a CU, FP64
-// four, by registers and LDS).
+// lines at their seams are read and written by one CU at one time.  Eight FP32
+// waves a block against one: 4096^2 456 against 560, 4096 x 1024 131 against
+// 144; on smaller grids, which fit such blocks less evenly, one is faster:
+// 2048 x 1024 78 against 82, 1200^2 59 against 63.  FP64 blocks have two waves
+// (four: 4096^2 728 against 698, 1200^2 90 against 84).  One block more than are
+// resident at once would run alone, so the chunks are as many as fit (FP32
+// eight waves a CU, FP64 four, by registers and LDS).
 //
 // Small grids go in tiles (pair_tile_kernel), above 256 sites and while there
-// is a CU for every block.  Measured as above, FP32: 8 x 64 3.7 -> 3.3,
-// 40 x 100 5.0 -> 3.3, 128 x 128 4.8 -> 3.5 (tiles of two rows), 160 x 300
-// 5.7 -> 4.3, 224 x 200 5.4 -> 4.2 (four); FP64: 8 x 64 5.5 -> 3.8, 40 x 100
-// 5.4 -> 3.8, 200 x 100 6.0 -> 4.4, 160 x 300 6.6 -> 5.2.  With more blocks
-// than CUs they lose: 256 x 512 FP32 7.3 -> 9.1, FP64 11.8 -> 13.2, and
-// 160 x 300 FP32 in tiles of two rows (450 blocks) 5.7.  Up to 256 sites one
-// block stepping alone (small_step_kernel) is faster: 8 x 16 2.7.
+// is a CU for every block.  Measured as above, FP32: 8 x 64 4.3 -> 3.5,
+// 40 x 100 5.0 -> 3.5, 128 x 128 5.0 -> 3.7 (tiles of two rows), 160 x 300
+// 5.7 -> 4.6, 224 x 200 5.6 -> 4.6 (four); FP64: 8 x 64 5.5 -> 4.0, 40 x 100
+// 5.3 -> 4.0, 200 x 100 5.9 -> 4.6, 160 x 300 6.5 -> 5.5.  With more blocks
+// than CUs they lose: 256 x 512 FP32 7.7 -> 11.7, FP64 11.5 -> 14.3.  That also
+// keeps tall grids of few columns on single steps, whose strips are mostly
+// margin: 8 x 4096 FP32 (512 tiles of eight rows) 10.4 -> 11.2, while 8 x 2048
+// (256) gains, 8.0 -> 6.3.  Up to 256 sites one block stepping alone
+// (small_step_kernel) takes them.
 constexpr size_t kPairTileMin = 256;
 constexpr int kPairHalo = 4;                    // columns on each side that only feed the others
 constexpr int kPairCols = 64 - 2 * kPairHalo;   // columns a wave owns
@@ -329,8 +331,10 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
       return L;
     }
   }
-  if (!forced && n < (size_t)(fp32 ? 1100000 : 500000)) return L;
-  L.nw = n > 3000000 ? (fp32 ? 8 : 4) : (fp32 ? 1 : 2);
+  if (!forced && n < (size_t)(fp32 ? 1200000 : 500000)) return L;
+  bool wide = n > 3000000;
+  if (const char *w = std::getenv("LBE_CSF_PAIR_NW")) wide = std::atoi(w) > 2;
+  L.nw = fp32 ? (wide ? 8 : 1) : 2;
   const int ngroups = ((p->nx + kPairCols - 1) / kPairCols + L.nw - 1) / L.nw;
   const int slots = kNumCUs * (fp32 ? 8 : 4) / L.nw;
   // strips fill their blocks evenly; a grid with few columns takes fewer
@@ -347,14 +351,16 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
 
 // Steps with two densities in one launch (density_step_kernel): strips and
 // chunks of one wave each; rows = 0 where they take two launches.  Taken from
-// 700k sites in FP32 and 500k in FP64.  Measured on MI355X, two launches ->
-// one, us per step, FP32: 4096^2 1313 -> 799, 2048^2 318 -> 215, 1500^2
-// 201 -> 146, 1030 x 777 49.0 -> 46.0, below the line 800^2 40.9 -> 40.5,
-// 512 x 1024 33.4 -> 36.1; FP64: 4096^2 2185 -> 1424, 1500^2 350 -> 226,
-// 1030 x 777 112 -> 85, 512 x 1024 57 -> 50, below it 320 x 600 24.2 -> 27.5
-// (ten rows of latency for chunks of four).  Above 3M sites neighbouring strips
-// march in step in one block, as in pair_launch: 4096^2 FP64 1791 with one wave
-// a block, 1424 with four; FP32 1126 and 799 with eight.
+// 1.35M sites in FP32 and 500k in FP64.  Measured on MI355X, two launches ->
+// one, us per step, FP32: 4096^2 1218 -> 994, 2048^2 326 -> 268, 1500^2
+// 207 -> 149, below the line 1300 x 1000 94.6 -> 94.8, 1200 x 1020 81 -> 88,
+// 1030 x 777 50 -> 55; FP64: 4096^2 2226 -> 1458, 1500^2 359 -> 225, 1030 x 777
+// 112 -> 85, 512 x 1024 56 -> 48, below it 320 x 600 23.8 -> 28.6 (ten rows of
+// latency for chunks of four).  The FP32 kernel needs 290 registers, so a CU
+// holds four of its waves too (held to 256 for eight it spills: 4096^2 1426).
+// Above 3M sites in FP64 neighbouring strips march in step in one block, as in
+// pair_launch: 4096^2 1777 with one wave a block, 1458 with four; the FP32 form
+// gains nothing by it (994 and 1167).
 constexpr int kDensityHalo = 3;
 inline PairLaunch density_launch(const lbe_csf_params *p, size_t state_bytes) {
   PairLaunch L{0, 0, 0, 0, 0, 0};
@@ -366,13 +372,15 @@ inline PairLaunch density_launch(const lbe_csf_params *p, size_t state_bytes) {
                         "LBE_CSF_TILE", "LBE_CSF_SMALL"})
     if (!forced && std::getenv(v)) return L;
   const size_t n = (size_t)p->nx * p->ny;
-  if (!forced && n < (size_t)(fp32 ? 700000 : 500000)) return L;
+  if (!forced && n < (size_t)(fp32 ? 1350000 : 500000)) return L;
   constexpr int cols = 64 - 2 * kDensityHalo;
-  L.nw = n > 3000000 ? (fp32 ? 8 : 4) : 1;
+  bool wide = n > 3000000;
+  if (const char *w = std::getenv("LBE_CSF_PAIR_NW")) wide = std::atoi(w) > 2;
+  L.nw = !fp32 && wide ? 4 : 1;
   const int ngroups = ((p->nx + cols - 1) / cols + L.nw - 1) / L.nw;
   const int wx = std::max(4, (p->nx + ngroups * L.nw - 1) / (ngroups * L.nw));
   L.nstrips = (p->nx + wx - 1) / wx;
-  const int chunks = std::max(1, kNumCUs * (fp32 ? 8 : 4) / L.nw / ngroups);
+  const int chunks = std::max(1, kNumCUs * 4 / L.nw / ngroups);
   L.rows = (p->ny + chunks - 1) / chunks;
   if (const char *r = std::getenv("LBE_CSF_PAIR_ROWS"))
     L.rows = std::max(1, std::min(p->ny, std::atoi(r)));

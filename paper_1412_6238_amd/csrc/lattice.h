@@ -39,21 +39,21 @@ enum : int {
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
-// Constants of a site's collision in the arithmetic type: formed on the host
-// in FP64 and rounded once, so that no lane divides or converts them.
+// Constants of a site's collision in the arithmetic type, formed on the host by
+// the operations that a lane would take.
 template <typename R>
 struct SiteConsts {
-  R omg, chg;         // 1 / tau_g and (tau_g - 1/2) 3 / rho
-  R omT, chT;         // the same of tau_T where it is constant
+  R wg, cg;           // 1 / tau_g and 1 - 1/(2 tau_g)
+  R wT, cT;           // the same of tau_T where it is constant
   R tauT0, dtauT;     // tau_T(c) = tauT0 + clamp(c) dtauT
-  R rho, rcv, i3rho;  // rho, rho cv, 3 / rho
-  R shift;            // rho cv Tg / 36 (FP32 form): change of reference of a
-                      // diagonal population that moves up one row
+  R rcv, irho;        // rho cv, 1 / rho
+  R wr, Tg;           // FP32 form: their product rho cv Tg / 36 is the change of reference
+                      // of a diagonal population that moves up one row
 };
 
 // Everything a step launch needs, passed by value.  Derived constants are
-// computed once on the host in FP64 and rounded to the kernel's arithmetic
-// type inside the kernel.
+// computed once on the host; those of the collision's FP32 part come rounded to
+// it (SiteConsts).
 struct StepArgs {
   const void *src;
   void *dst;
@@ -62,9 +62,8 @@ struct StepArgs {
   const double *twb, *twt;  // wall temperatures [nx]
   // physical and derived constants
   double rho, cv, rcv;      // rho, cv, rho*cv
-  double inv_rho, inv_rcv, rho3;   // 1/rho, 1/(rho cv), rho/3
-  double omf, chf;          // 1/tau_f and tau_f - 1/2 where tau_f is constant
-  double epsT;              // eps alpha sigmaT, with the sign of the Marangoni term
+  double inv_rho, inv_rcv, rho3;   // 1/rho, 1/(rho cv), rho (1/3)
+  double wf, cf;            // 1/tau_f and 1 - 1/(2 tau_f) where tau_f is constant
   SiteConsts<float> kf;
   SiteConsts<double> kd;
   int vartau;               // tau_f or tau_T varies with c

@@ -97,18 +97,24 @@ int fail(lbe_csf *h, int code, const std::string &msg) {
   } while (0)
 
 template <typename R>
-void fill_site_consts(const StepArgs &a, SiteConsts<R> &k) {
-  const double i3rho = 3.0 / a.rho, tau_g = 1.0 / a.omg_g;
-  k.omg = R(a.omg_g);
-  k.chg = R((tau_g - 0.5) * i3rho);
-  k.omT = R(1.0 / a.tauT0);
-  k.chT = R((a.tauT0 - 0.5) * i3rho);
+void fill_site_consts(const StepArgs &a, bool tile, SiteConsts<R> &k) {
+  k.wg = R(a.omg_g);
+  k.cg = R(1) - R(0.5) * k.wg;
   k.tauT0 = R(a.tauT0);
   k.dtauT = R(a.dtauT);
-  k.rho = R(a.rho);
+  k.wT = R(1) / k.tauT0;
+  k.cT = R(1) - R(0.5) * k.wT;
   k.rcv = R(a.rcv);
-  k.i3rho = R(i3rho);
-  k.shift = R(a.rcv * a.Tg / 36.0);
+  k.irho = R(a.inv_rho);
+  // on grids of the tile kernel the product stays inside the fused
+  // multiply-add, elsewhere it is rounded by itself: which one a grid has is
+  // part of its FP32 states' bits, whichever kernel takes its steps
+  k.wr = wq<R>(5) * k.rcv;
+  k.Tg = R(a.Tg);
+  if (!tile) {
+    k.wr *= k.Tg;
+    k.Tg = R(1);
+  }
 }
 
 void fill_constants(lbe_csf *h) {
@@ -154,13 +160,13 @@ void fill_constants(lbe_csf *h) {
   a.partials = h->partials;
   a.inv_rho = 1.0 / a.rho;
   a.inv_rcv = 1.0 / a.rcv;
-  a.rho3 = a.rho / 3.0;
-  a.omf = 1.0 / a.tauf0;
-  a.chf = a.tauf0 - 0.5;
-  a.epsT = a.epsalpha * a.sigmaT;
+  a.rho3 = a.rho * (1.0 / 3.0);
+  a.wf = 1.0 / a.tauf0;
+  a.cf = 1.0 - 0.5 * a.wf;
   a.vartau = a.dtauf != 0.0 || a.dtauT != 0.0;
-  fill_site_consts(a, a.kf);
-  fill_site_consts(a, a.kd);
+  const bool tile = use_tile_kernel(&p);
+  fill_site_consts(a, tile, a.kf);
+  fill_site_consts(a, tile, a.kd);
 }
 
 template <typename S, typename R, bool DEV, int MODE, int PIPE>
@@ -350,23 +356,21 @@ int launch_density(lbe_csf *h, bool diag) {
   const int nb = h->density.nblocks;
   hipStream_t st = h->stream;
   constexpr int V = kStore | kVarRho;
-  auto go = [&](auto form, auto waves) {
-    constexpr int F = decltype(form)::value, W = decltype(waves)::value;
-    constexpr int W64 = W > 4 ? 4 : W;
-    if (f64 && diag)
-      density_step_kernel<double, double, false, V | F | kDiag, W64><<<nb, 64 * W64, 0, st>>>(a);
-    else if (f64) density_step_kernel<double, double, false, V | F, W64><<<nb, 64 * W64, 0, st>>>(a);
-    else if (diag) density_step_kernel<float, float, true, V | F | kDiag, W><<<nb, 64 * W, 0, st>>>(a);
-    else density_step_kernel<float, float, true, V | F, W><<<nb, 64 * W, 0, st>>>(a);
+  auto go = [&](auto form) {
+    constexpr int F = decltype(form)::value;
+    if (f64 && h->density.nw > 1) {
+      if (diag) density_step_kernel<double, double, false, V | F | kDiag, 4><<<nb, 256, 0, st>>>(a);
+      else density_step_kernel<double, double, false, V | F, 4><<<nb, 256, 0, st>>>(a);
+    } else if (f64) {
+      if (diag) density_step_kernel<double, double, false, V | F | kDiag, 1><<<nb, 64, 0, st>>>(a);
+      else density_step_kernel<double, double, false, V | F, 1><<<nb, 64, 0, st>>>(a);
+    } else {
+      if (diag) density_step_kernel<float, float, true, V | F | kDiag, 1><<<nb, 64, 0, st>>>(a);
+      else density_step_kernel<float, float, true, V | F, 1><<<nb, 64, 0, st>>>(a);
+    }
   };
-  constexpr std::integral_constant<int, kCurv> curvature{};
-  constexpr std::integral_constant<int, 0> potential{};
-  constexpr std::integral_constant<int, 1> one{};
-  constexpr std::integral_constant<int, 8> wide{};
-  if (curv && h->density.nw > 1) go(curvature, wide);
-  else if (curv) go(curvature, one);
-  else if (h->density.nw > 1) go(potential, wide);
-  else go(potential, one);
+  if (curv) go(std::integral_constant<int, kCurv>{});
+  else go(std::integral_constant<int, 0>{});
   HIPCHK(h, hipGetLastError());
   return LBE_CSF_OK;
 }
@@ -471,9 +475,7 @@ int launch_pair(lbe_csf *h, bool diag, void *tape = nullptr, void *tape2 = nullp
     else if (f64) launch_pair_tiles<double, false, 0>(h, a, diag, tape != nullptr);
     else if (curv) launch_pair_tiles<float, true, kCurv>(h, a, diag, tape != nullptr);
     else launch_pair_tiles<float, true, 0>(h, a, diag, tape != nullptr);
-  } else if (f64 && curv && wide) launch_pair_as<double, false, kCurv, 4>(h, a, diag, tape != nullptr);
-  else if (f64 && curv) launch_pair_as<double, false, kCurv, 2>(h, a, diag, tape != nullptr);
-  else if (f64 && wide) launch_pair_as<double, false, 0, 4>(h, a, diag, tape != nullptr);
+  } else if (f64 && curv) launch_pair_as<double, false, kCurv, 2>(h, a, diag, tape != nullptr);
   else if (f64) launch_pair_as<double, false, 0, 2>(h, a, diag, tape != nullptr);
   else if (curv && wide) launch_pair_as<float, true, kCurv, 8>(h, a, diag, tape != nullptr);
   else if (curv) launch_pair_as<float, true, kCurv, 1>(h, a, diag, tape != nullptr);

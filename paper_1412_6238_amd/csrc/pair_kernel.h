@@ -287,7 +287,7 @@ pair_step_kernel(const StepArgs a) {
       const PairTape<R> tape(a.tape, (uint32_t)n, (uint32_t)(wrap_row(r) * nx), x,
                              owned && r >= y0 && r < y1);
       const bool bot = EDGE && walls && r == 0, top = EDGE && walls && r == ny - 1;
-      site_collide<R, DEV, kMode1, EDGE, false>(
+      site_collide<R, DEV, kMode1, EDGE>(
           a, wrap_row(r), x, bot, top, &l.c[0][sS][lane], &l.c[0][sC][lane], &l.c[0][sN][lane],
           &l.t[0][sS][lane], &l.t[0][sC][lane], &l.t[0][sN][lane], &l.p[0][sS][lane],
           &l.p[0][sC][lane], &l.p[0][sN][lane], cur, acc,
@@ -368,7 +368,7 @@ pair_step_kernel(const StepArgs a) {
       out.rb1 = rb1;
       out.bot = bot;
       out.top = top;
-      site_collide<R, DEV, kMode, EDGE, false>(
+      site_collide<R, DEV, kMode, EDGE>(
           a, jw, x, bot, top, &l.c[1][sS][lane], &l.c[1][sC][lane], &l.c[1][sN][lane],
           &l.t[1][sS][lane], &l.t[1][sC][lane], &l.t[1][sN][lane], &l.p[1][sS][lane],
           &l.p[1][sC][lane], &l.p[1][sN][lane], f1, acc,
@@ -524,7 +524,7 @@ pair_tile_kernel(const StepArgs a) {
   // FP32: a wave takes the form with walls only where its own row touches one
   // (in FP64 the two forms together spill registers)
   auto collide = [&](auto mode, auto wall, auto &&sink) __attribute__((always_inline)) {
-    site_collide<R, DEV, decltype(mode)::value, decltype(wall)::value, false>(
+    site_collide<R, DEV, decltype(mode)::value, decltype(wall)::value>(
         a, jr, x, bot, top, &l.c[row - 1][lane], &l.c[row][lane], &l.c[row + 1][lane],
         &l.t[row - 1][lane], &l.t[row][lane], &l.t[row + 1][lane], &l.p[row - 1][lane],
         &l.p[row][lane], &l.p[row + 1][lane], cur, acc, sink);

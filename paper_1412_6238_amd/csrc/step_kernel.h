@@ -176,51 +176,92 @@ __device__ __forceinline__ void site_moments(const RowVals<R> &r, double inv_rcv
   *p = f;
 }
 
-// One pair of opposite directions (i, o) of one lattice: with xi = xi_i,
-// b = 3 xi.u, Q = b^2/2 - 3/2 u^2 and a force vector X already times
-// (tau - 1/2), equilibrium and forcing of the pair are w (E + O) and
-// w (E - O),
-//   E = K0 + K1 Q + b X1.xi,   O = K1 b + X0.xi + Q X1.xi
-// (X1 differs from X0 only by the density terms of Eq. 6), and a population
-// relaxes as v - om (v - w (E +- O)): one difference of nearby values and
-// one fused multiply-add each.
-template <typename R>
-struct PairEq {
-  R E, O;
+// X.(xi_i - u) of a vector X.  Which product is fused is part of a state's
+// bits (site_collide), and differs between the momentum equation (MOM) and the
+// other two in directions 0 and 2.
+template <typename T, bool MOM>
+struct ForceDot {
+  T x, y, ux, uy;
+  __device__ __forceinline__ T operator()(int i) const {
+#pragma clang fp contract(off)
+    const T xp = T(1) - ux, xm = T(-1) - ux, yp = T(1) - uy, ym = T(-1) - uy;
+    switch (i) {
+      case 0: return MOM ? fma_(x, -ux, y * -uy) : x * -ux + y * -uy;
+      case 1: return fma_(x, xp, y * -uy);
+      case 2: return MOM ? fma_(y, yp, x * -ux) : fma_(x, -ux, y * yp);
+      case 3: return fma_(x, xm, y * -uy);
+      case 4: return fma_(y, ym, x * -ux);
+      case 5: return x * xp + y * yp;
+      case 6: return x * xm + y * yp;
+      case 7: return x * xm + y * ym;
+      default: return x * xp + y * ym;
+    }
+  }
 };
-template <typename R>
-__device__ __forceinline__ PairEq<R> pair_eq(R b, R Q, R K0, R K1, R X0, R X1) {
-  return {fma_(Q, K1, fma_(b, X1, K0)), fma_(b, K1, fma_(X1, Q, X0))};
-}
-template <typename R>
-__device__ __forceinline__ R relax(R v, R w, R eq, R om) {
-  return fma_(-om, fma_(-w, eq, v), v);
+
+// Gamma_i(u) = w_i (1 + t_i), t_i = 3 e + 9/2 e^2 - 3/2 u^2 with e = xi_i.u;
+// opposite directions share 9/2 e^2.
+template <typename T>
+struct GammaPoly {
+  T e[4], q[4], usq, usq15;   // of directions 1, 2, 5, 6
+  __device__ __forceinline__ GammaPoly(T ux, T uy) {
+#pragma clang fp contract(off)
+    usq = fma_(ux, ux, uy * uy);
+    usq15 = T(1.5) * usq;
+    e[0] = ux;
+    e[1] = uy;
+    e[2] = ux + uy;
+    e[3] = uy - ux;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) q[m] = e[m] * (T(4.5) * e[m]);
+  }
+  __device__ __forceinline__ T operator()(int i) const {
+#pragma clang fp contract(off)
+    if (i == 0) return -usq15;
+    const int m = i < 5 ? (i - 1) & 1 : 2 + ((i - 5) & 1);
+    const bool opposite = i == 3 || i == 4 || i == 7 || i == 8;
+    const T t = fma_(T(3), opposite ? -e[m] : e[m], q[m]);
+    return i < 3 ? fma_(T(-1.5), usq, t) : t - usq15;
+  }
+};
+
+// a / b, correctly rounded, given inv = 1/b correctly rounded: the quotient
+// a inv is within one unit of the last place, and one residual corrects it
+// (P. Markstein, Computation of elementary functions on the IBM RISC System/6000
+// processor, IBM J. Res. Dev. 34 (1990), Theorem 7.1)
+__device__ __forceinline__ double quotient(double a, double b, double inv) {
+  const double q = a * inv;
+  return fma_(fma_(-b, q, a), inv, q);
 }
 
 // Moments, stencils, closures and collision of site (x, j), with its
 // diagnostics and field output.  With kStore the post-collision values go to
-// sink(i, lattice, value) as they are formed, so that their stores spread over
-// the collision, and the two rest populations to sink.rest(g0, h0); with kTape the moments go to sink.tape.  The
-// directions come pair by pair, or with BYDIR in their order 1, 2, 3, ...,
-// which holds two pairs at a time: the row-marching FP32 step on 4096^2 stores
-// 2.5% faster that way (737 against 756 us), the two-step kernel has no
-// registers for it (470 against 406 us).  A value of hbar already holds the
-// deviation against the reference of the row it moves to and, in a direction
-// that a wall reflects, the wall term of the anti-bounce-back.  cS/cC/cN,
-// tS.., pS.. point at the ring entries west of the site in rows j-1, j, j+1
-// (index 0 west, 1 centre, 2 east).  bot and top: the row touches that wall
-// (never without WALL).
+// sink(i, lattice, value) as they are formed, direction by direction, so that
+// their stores spread over the collision, and the two rest populations to
+// sink.rest(g0, h0); with kTape the moments go to sink.tape.  A value of hbar
+// already holds the deviation against the reference of the row it moves to
+// and, in a direction that a wall reflects, the wall term of the
+// anti-bounce-back.  cS/cC/cN, tS.., pS.. point at the ring entries west of the
+// site in rows j-1, j, j+1 (index 0 west, 1 centre, 2 east).  bot and top: the
+// row touches that wall (never without WALL).
+//
+// The bits of a state are fixed here: sums run in the order written, and
+// multiply-adds are fused where written and nowhere else, so that every kernel
+// that inlines this gives the same state.  A change of that order is a change
+// of output: the droplet velocity u_r = sum c u_y / sum c of a short run is the
+// residue of a sum that cancels over five orders of magnitude, and carries the
+// rounding of every FP32 population (1e-3 of it after one step from a droplet
+// at rest).  An evaluation by even and odd parts of opposite directions, with
+// the forcing folded into the equilibrium, takes a fifth fewer instructions;
+// it is as exact in the fields but not the same in u_r, and its FP64 error
+// against 64-bit evaluations of the printed form is 1.2 to 1.7 times as large.
 //
 // What bounds it: vector instructions (one wave64 FP32 or FP64 operation
-// takes four cycles of a SIMD), and on small grids their dependent chain.  So
-// opposite directions share their even and odd parts (pair_eq: 11 operations
-// and 3 a population, for each of the three lattices), the Marangoni term
-// eps alpha (|grad c|^2 grad s - (grad c.grad s) grad c) is written as the
-// equal eps alpha (gcy, -gcx) (gcy gsx - gcx gsy), and constants derived from
-// the parameters come from the host (StepArgs).  Multiply-adds are fused
-// where written and nowhere else, so that every kernel that inlines this
-// gives the same bits.
-template <typename R, bool DEV, int MODE, bool WALL, bool BYDIR, typename Sink>
+// takes four cycles of a SIMD), and on small grids their dependent chain.
+// Constants derived from the parameters come from the host (StepArgs),
+// quotients by constants are products and one correction, and opposite
+// directions share what is even in u.
+template <typename R, bool DEV, int MODE, bool WALL, typename Sink>
 __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bool bot, bool top,
                                              const double *cS, const double *cC, const double *cN,
                                              const R *tS, const R *tC, const R *tN, const R *pS,
@@ -231,27 +272,30 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
   const SiteConsts<R> &k = site_consts<R>(a);
   // order parameter and its stencils in FP64
   const double cd = cC[1];
-  double gcx, gcy, mu, tHt = 0.0;
+  double gcx, gcy, mu, tHt = 0.0, g2;
   {
     const double e = cC[2], w = cC[0], nn = cN[1], s = cS[1];
     const double ne = cN[2], nw = cN[0], sw = cS[0], se = cS[2];
-    const double d1 = ne - sw, d2 = se - nw;
-    gcx = fma_(e - w, 1.0 / 3.0, (d1 + d2) * (1.0 / 12.0));
-    gcy = fma_(nn - s, 1.0 / 3.0, (d1 - d2) * (1.0 / 12.0));
+    gcx = fma_(e - w, 1.0 / 3.0, (ne + se - nw - sw) * (1.0 / 12.0));
+    gcy = fma_(nn - s, 1.0 / 3.0, (ne + nw - se - sw) * (1.0 / 12.0));
+    g2 = fma_(gcy, gcy, gcx * gcx);
     const double dx2 = (e - cd) + (w - cd), dy2 = (nn - cd) + (s - cd);
-    const double dd = (ne - cd) + (nw - cd) + (se - cd) + (sw - cd);
-    const double lap = fma_(dx2 + dy2, 2.0 / 3.0, dd * (1.0 / 6.0));
-    mu = fma_(a.beta2 * (cd * (cd - 1.0)), fma_(2.0, cd, -1.0), -a.eps2 * lap);
+    const double dsum = (ne - cd) + (nw - cd) + (se - cd) + (sw - cd), dd = dsum * (1.0 / 6.0);
+    const double lap = fma_(2.0 / 3.0, dx2 + dy2, dd);
+    mu = fma_(fma_(2.0, cd, -1.0), (cd - 1.0) * (a.beta2 * cd), -(a.eps2 * lap));
     if (MODE & kCurv) {
       // Hessian of c on the same nine points (exact on quadratics) and the
       // second derivative along the unit tangent t = (-gy, gx)/|grad c|,
       // which equals |grad c| div n for n = grad c/|grad c|
-      const double hxx = fma_(2.0 / 3.0, dx2, fma_(-1.0 / 3.0, dy2, dd * (1.0 / 6.0)));
-      const double hyy = fma_(2.0 / 3.0, dy2, fma_(-1.0 / 3.0, dx2, dd * (1.0 / 6.0)));
+      // (a step rounds its diagonal part once more than the launches that only
+      // evaluate a state; which bits those give is part of their output too)
+      const double ax = fma_(2.0 / 3.0, dx2, -((1.0 / 3.0) * dy2));
+      const double ay = fma_(2.0 / 3.0, dy2, -((1.0 / 3.0) * dx2));
+      const double hxx = (MODE & kStore) ? ax + dd : fma_(1.0 / 6.0, dsum, ax);
+      const double hyy = (MODE & kStore) ? ay + dd : fma_(1.0 / 6.0, dsum, ay);
       const double hxy = 0.25 * ((ne - nw) - (se - sw));
-      const double gg = fma_(gcx, gcx, gcy * gcy);
-      if (gg > 0.0)
-        tHt = fma_(gcy * gcy, hxx, fma_(-2.0 * gcx * gcy, hxy, gcx * gcx * hyy)) / gg;
+      if (g2 > 0.0)
+        tHt = fma_(hyy, gcx * gcx, fma_(gcy * gcy, hxx, -(2.0 * gcx * gcy * hxy))) / g2;
     }
   }
   const R Tv = tC[1];   // T, or Delta T = T - Trow in the FP32 form
@@ -266,9 +310,9 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
   // arithmetic, not the storage, would otherwise set the error.
   auto grad = [](const R *Sr, const R *Cr, const R *Nr, double *gx, double *gy) {
 #pragma clang fp contract(off)
-    const double d1 = double(Nr[2]) - double(Sr[0]), d2 = double(Sr[2]) - double(Nr[0]);
-    *gx = fma_(double(Cr[2]) - double(Cr[0]), 1.0 / 3.0, (d1 + d2) * (1.0 / 12.0));
-    *gy = fma_(double(Nr[1]) - double(Sr[1]), 1.0 / 3.0, (d1 - d2) * (1.0 / 12.0));
+    const double ne = Nr[2], nw = Nr[0], se = Sr[2], sw = Sr[0];
+    *gx = fma_(double(Cr[2]) - double(Cr[0]), 1.0 / 3.0, (ne + se - nw - sw) * (1.0 / 12.0));
+    *gy = fma_(ne + nw - se - sw, 1.0 / 12.0, (double(Nr[1]) - double(Sr[1])) * (1.0 / 3.0));
   };
   double gTx, gTy, gpx, gpy;
   grad(tS, tC, tN, &gTx, &gTy);
@@ -277,29 +321,32 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
   double fv[9];
 #pragma unroll
   for (int q = 0; q < 9; ++q) fv[q] = double(cur.v[q]);
-  const double m5 = fv[5] - fv[7], m6 = fv[6] - fv[8];
-  const double jx = (fv[1] - fv[3]) + (m5 - m6), jy = (fv[2] - fv[4]) + (m5 + m6);
+  const double jx = fv[1] - fv[3] + fv[5] - fv[6] - fv[7] + fv[8];
+  const double jy = fv[2] - fv[4] + fv[5] + fv[6] - fv[7] - fv[8];
   if constexpr ((MODE & kTape) != 0) sink.tape(cd, Tv, pv, R(jx), R(jy));
   // closures: sigma = sigma0 - sigmaT (T - Tref)
-  const double sigma = fma_(-a.sigmaT, double(Tv) + (Trow - a.Tref), a.sigma0);
+  const double Tm = DEV ? double(Tv) + (Trow - a.Tref) : double(Tv) - a.Tref;
+  const double sigma = fma_(-a.sigmaT, Tm, a.sigma0);
+  const double gsx = -a.sigmaT * gTx, gsy = -a.sigmaT * gTy;
+  const double gds = fma_(gcx, gsx, gcy * gsy);
   // capillary part along grad c: kcap sigma mu (potential form) or
   // -sigma eps alpha |grad c| div n (curvature form)
   const double ks = (MODE & kCurv) ? -a.epsalpha * sigma * tHt : a.kcap * sigma * mu;
-  // Marangoni part, grad sigma = -sigmaT grad T
-  const double mg = a.epsT * fma_(gcx, gTy, -(gcy * gTx));
   // two densities: rho(c) = rho + c drho, grad rho = drho grad c
   const double rho_s = VR ? fma_(cd, a.drho, a.rho) : a.rho;
   const double inv_rho = VR ? 1.0 / rho_s : a.inv_rho;
-  const double Fx = fma_(ks, gcx, fma_(mg, gcy, rho_s * a.ax));
-  const double Fy = fma_(ks, gcy, fma_(-mg, gcx, rho_s * a.ay));
-  // u = (3 j + F / 2) / rho
-  const double uxd = fma_(0.5, Fx, 3.0 * jx) * inv_rho, uyd = fma_(0.5, Fy, 3.0 * jy) * inv_rho;
   const double grx = VR ? a.drho * gcx : 0.0, gry = VR ? a.drho * gcy : 0.0;
+  const double Fx = fma_(rho_s, a.ax, fma_(ks, gcx, a.epsalpha * fma_(g2, gsx, -(gds * gcx))));
+  const double Fy = fma_(rho_s, a.ay, fma_(ks, gcy, a.epsalpha * fma_(g2, gsy, -(gds * gcy))));
+  // u = (3 j + F / 2) / rho
+  const double uxd = fma_(3.0 * jx, inv_rho, 0.5 * Fx * inv_rho);
+  const double uyd = fma_(3.0 * jy, inv_rho, 0.5 * Fy * inv_rho);
   if constexpr ((MODE & kPress) != 0) {
     // the pressure of Eq. 9: p = sum f + (1/2) u.grad(rho cs^2)
     sink.pressure(fma_(0.5 / 3.0, fma_(uxd, grx, uyd * gry), double(pv)));
     return;
   }
+  const R ux = R(uxd), uy = R(uyd);
   if (MODE & kDiag) {
     const double Td = DEV ? double(Tv) + Trow : double(Tv);
     const double yy = double(j) + 0.5, xx = double(x) + 0.5;
@@ -309,184 +356,124 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
     acc[3] = fma_(cd, xx, acc[3]);
     if (cd >= 0.5) {
       acc[4] += cd;
-      acc[5] = fma_(cd, double(R(uyd)), acc[5]);
+      acc[5] = fma_(cd, double(uy), acc[5]);
     }
-    const double chk = cd + Td + double(pv) + double(R(uxd)) + double(R(uyd));
+    const double chk = cd + Td + double(pv) + double(ux) + double(uy);
     if (!isfinite(chk)) acc[6] += 1.0;
   }
   if (MODE & kFields) {
     const size_t s = (size_t)j * a.nx + x;
     if (a.phi) a.phi[s] = fma_(2.0, cd, -1.0);
-    if (a.ux) a.ux[s] = double(R(uxd));
-    if (a.uy) a.uy[s] = double(R(uyd));
+    if (a.ux) a.ux[s] = double(ux);
+    if (a.uy) a.uy[s] = double(uy);
     if (a.p) a.p[s] = DEV ? double(pv) + a.p0 : double(pv);
     if (a.T) a.T[s] = DEV ? double(Tv) + Trow : double(Tv);
   }
   if (!(MODE & kStore)) return;
 
-  // relaxation: rates om = 1/tau and the forcing factors tau - 1/2, times
-  // 3/rho in the g and hbar equations (F enters as F/(rho cs^2))
+  // relaxation rates 1/tau and the factors 1 - 1/(2 tau) of the forcing, the
+  // latter times 3/rho in the hbar equation (F enters as F/(rho cs^2))
   const R c = R(cd);
-  double omf = a.omf, chf = a.chf;
-  R omT = k.omT, chT = k.chT;
+  const R irho = VR ? R(inv_rho) : k.irho;
+  double wf = a.wf, cf = a.cf;
+  R wT = k.wT, cT = k.cT;
   if (a.vartau) {
     const R ch = c < R(0) ? R(0) : (c > R(1) ? R(1) : c);
-    const double tf = fma_(double(ch), a.dtauf, a.tauf0);
-    const R tT = fma_(ch, k.dtauT, k.tauT0);
-    omf = 1.0 / tf;
-    chf = tf - 0.5;
-    omT = R(1) / tT;
-    chT = (tT - R(0.5)) * k.i3rho;
+    wf = 1.0 / fma_(double(ch), a.dtauf, a.tauf0);
+    cf = fma_(wf, -0.5, 1.0);
+    wT = R(1) / fma_(ch, k.dtauT, k.tauT0);
+    cT = fma_(wT, R(-0.5), R(1));
   }
-  const R irho_r = VR ? R(inv_rho * a.rho) : R(1);   // two densities: rho / rho(c)
-  const double rcvd = VR ? rho_s * a.cv : a.rcv;
+  const R sh = R(3) * irho * cT;
+  const R sg = k.cg * (R(3) * c * irho);
+  // temperature in FP64
+  double hs = 0.0;
+#pragma unroll
+  for (int q = 1; q < 9; ++q) hs += double(cur.v[18 + q]);
+  const double rcvd = VR ? a.cv * rho_s : a.rcv;
   const R rcv = VR ? R(rcvd) : k.rcv;
   // two densities, FP32 form: the deviations are taken from w rho cv Trow
   // with the density of the c = 0 fluid; hoff = (rho(c) - rho) cv Trow
-  const R hoff = (VR && DEV) ? R(cd * a.drho * a.cv * Trow) : R(0);
+  const double hoffc = (VR && DEV) ? a.cv * (cd * a.drho) : 0.0;
+  const R hoff = (VR && DEV) ? R(hoffc * Trow) : R(0);
+  const double hsum = (VR && DEV) ? fma_(-hoffc, Trow, cur.h0() + hs) : cur.h0() + hs;
+  const double Td = VR ? hsum / rcvd : quotient(hsum, rcvd, a.inv_rcv);   // T or Delta T
+  const R Tfull = R(DEV ? Td + Trow : Td);
+  const R rcvT = rcv * Tfull;
+  const R gmu = R(a.gam3 * mu);
+  // F - grad p drives c (Eq. 12); Fbar = grad(rho cs^2) - grad p + F drives
+  // hbar (Sec. III)
+  const double Bx = Fx - gpx, By = Fy - gpy;
+  const ForceDot<double, true> dF{Fx, Fy, uxd, uyd}, dR{grx, gry, uxd, uyd};
+  const ForceDot<R, false> dB{R(Bx), R(By), ux, uy};
+  const ForceDot<R, false> dH{VR ? R(Bx + quotient(grx, 3.0, 1.0 / 3.0)) : R(Bx),
+                              VR ? R(By + quotient(gry, 3.0, 1.0 / 3.0)) : R(By), ux, uy};
+  const GammaPoly<double> tf(uxd, uyd);
+  const GammaPoly<R> tg(ux, uy);
+  const double rho3 = VR ? rho_s * (1.0 / 3.0) : a.rho3;
   // a direction that the wall reflects stores 2 w (rho cv T_wall [+ hoff]) -
   // hbar; elsewhere the value itself (factor 1, wall term 0)
-  R su = 1, wu = 0, sd = 1, wdn = 0;
+  R su = 1, sd = 1, bu = 0, bd = 0;
   if (WALL && (bot || top)) {
-    const R twv = R((bot ? a.twb : a.twt)[x] - Trow);
-    const R wall = R(2.0 / 36.0) * (VR ? fma_(rcv, twv, hoff) : rcv * twv);
+    R tw = R((bot ? a.twb : a.twt)[x] - Trow);
+    if (VR && DEV) tw = fma_(rcv, tw, hoff);
     if (top) {
       su = -1;
-      wu = wall;
+      bu = tw;
     } else {
       sd = -1;
-      wdn = wall;
+      bd = tw;
     }
   }
-
-  // f (Eqs. 6-7) in FP64: f^eq = w p + rho cs^2 G with G = w (b + Q).  Near an
-  // interface the forcing term carries the capillary force, which the
-  // pressure gradient balances; FP32 weights and Gamma_i would leave a
-  // relative bias of ~1e-8 in that balance, a spurious force whose viscous
-  // response grows over R^2 / nu steps.
-  // pairs of directions (1, 3), (2, 4), (5, 7), (6, 8)
-  const double bx = 3.0 * uxd, by = 3.0 * uyd;
-  const double mh = -1.5 * fma_(uxd, uxd, uyd * uyd);
-  const double X0x = chf * Fx, X0y = chf * Fy;
-  const double X0u = fma_(X0x, uxd, X0y * uyd);
-  // with two densities the forcing adds (xi - u).grad(rho cs^2)
-  // (Gamma_i(u) - Gamma_i(0)) (Eq. 6); Gamma_i(0) = w_i
-  const double cr = VR ? chf * (1.0 / 3.0) : 0.0;
-  const double X1x = VR ? fma_(cr, grx, X0x) : X0x, X1y = VR ? fma_(cr, gry, X0y) : X0y;
-  const double X1u = VR ? fma_(X1x, uxd, X1y * uyd) : X0u;
-  const double fK0 = double(pv) - X0u;
-  const double fK1 = (VR ? rho_s * (1.0 / 3.0) : a.rho3) - X1u;
-  const double bf[4] = {bx, by, bx + by, by - bx};
-  const double X0[4] = {X0x, X0y, X0x + X0y, X0y - X0x};
-  const double X1[4] = {X1x, X1y, VR ? X1x + X1y : X0[2], VR ? X1y - X1x : X0[3]};
-  // g (Eqs. 12-14): g^eq_0 = c - (1 - w0) 3 Gamma mu + c G_0,
-  // g^eq_i = w_i 3 Gamma mu + c G_i, forced by F - grad p; hbar (Eqs. 22, 25):
-  // h^eq = rho cv T Gamma_i, forced by Fbar = F - grad p + grad(rho cs^2)
-  const R ux = R(uxd), uy = R(uyd);
-  const R bxr = R(3) * ux, byr = R(3) * uy;
-  const R mhr = R(-1.5) * fma_(ux, ux, uy * uy);
-  const R gmu = R(a.gam3 * mu);
-  const double Bx = Fx - gpx, By = Fy - gpy;
-  const R Tfull = DEV ? R(double(Tv) + Trow) : Tv;
-  const R rcvT = rcv * Tfull;
-  const R chg = VR ? k.chg * c * irho_r : k.chg * c;
-  const R chh = VR ? chT * rcvT * irho_r : chT * rcvT;
-  const R Gx = chg * R(Bx), Gy = chg * R(By);
-  const R Hx = chh * (VR ? R(fma_(grx, 1.0 / 3.0, Bx)) : R(Bx));
-  const R Hy = chh * (VR ? R(fma_(gry, 1.0 / 3.0, By)) : R(By));
-  const R Gu = fma_(Gx, ux, Gy * uy), Hu = fma_(Hx, ux, Hy * uy);
-  const R gK0 = gmu - Gu, gK1 = c - Gu;
-  const R hK0 = DEV ? (VR ? fma_(rcv, Tv, hoff) - Hu : fma_(rcv, Tv, -Hu)) : rcvT - Hu;
-  const R hK1 = rcvT - Hu;
-  const R b[4] = {bxr, byr, bxr + byr, byr - bxr};
-  const R XG[4] = {Gx, Gy, Gx + Gy, Gy - Gx};
-  const R XH[4] = {Hx, Hy, Hx + Hy, Hy - Hx};
-  // FP32 form: a move to the next row changes the reference of hbar by
-  // w rho cv Tg xi_y (not for the populations that a wall reflects)
-  const R sup = DEV && !(WALL && top) ? k.shift : R(0);
-  const R sdn = DEV && !(WALL && bot) ? -k.shift : R(0);
   // FP32 form: what the eight moving populations of g and hbar give away in
   // this collision, as stored (sum of old - new, each difference of two
   // nearby FP32 values)
   R dg = 0, dh = 0;
-  auto emit_f = [&](int i, double eq) { sink(i, 0, R(relax(fv[i], wq<double>(i), eq, omf))); };
-  // g and hbar of one direction; eg and eh receive what they give away
-  auto emit_gh = [&](int i, R ge, R he, R &eg, R &eh) {
-#pragma clang fp contract(off)
-    const R w = wq<R>(i), gv = cur.v[9 + i], hv = cur.v[18 + i];
-    const R gn = relax(gv, w, ge, k.omg);
-    R hn = relax(hv, w, he, omT);
-    if (DEV) {
-      eg = gv - gn;
-      if (kEy[i] != 0) {
-        const R sh = (kEy[i] > 0 ? sup : sdn) * (i < 5 ? R(4) : R(1));   // w = 4/36 or 1/36
-        hn -= sh;
-        eh = (hv - hn) - sh;
-      } else {
-        eh = hv - hn;
-      }
+#pragma unroll
+  for (int i = 0; i < 9; ++i) {
+    // f (Eqs. 6-7): f^eq = w p + rho cs^2 G, G = Gamma_i - w_i, in FP64.  Near
+    // an interface the forcing term carries the capillary force, which the
+    // pressure gradient balances; FP32 weights and Gamma_i would leave a
+    // relative bias of ~1e-8 in that balance, a spurious force whose viscous
+    // response grows over R^2 / nu steps.
+    {
+      const double w = wq<double>(i), t = tf(i), G = w * t, gam = fma_(w, t, w);
+      const double feq = i == 0 ? fma_(w, double(pv), rho3 * G) : fma_(rho3, G, w * double(pv));
+      // with two densities the forcing adds (xi - u).grad(rho cs^2)
+      // (Gamma_i(u) - Gamma_i(0)) (Eq. 6); Gamma_i(0) = w_i
+      const double src = VR ? fma_(dR(i) * (1.0 / 3.0), G, dF(i) * gam) : dF(i) * gam;
+      sink(i, 0, R(fma_(cf, src, fma_(-wf, fv[i] - feq, fv[i]))));
     }
+    if (i == 0) continue;
+    // g (Eqs. 12-14): g^eq_i = w_i 3 Gamma mu + c G_i
+    const R w = wq<R>(i), t = tg(i), G = w * t, gam = fma_(w, t, w);
+    const R gv = cur.v[9 + i], hv = cur.v[18 + i];
+    const R gn = fma_(sg * dB(i), gam, fma_(-k.wg, gv - fma_(c, G, w * gmu), gv));
     sink(i, 1, gn);
-    if (!WALL || kEy[i] == 0)
-      sink(i, 2, hn);
-    else
-      sink(i, 2, fma_(kEy[i] > 0 ? su : sd, hn, (kEy[i] > 0 ? wu : wdn) * (i < 5 ? R(4) : R(1))));
-  };
-  auto give = [&](R eg, R eh) {
-#pragma clang fp contract(off)
+    // hbar (Eqs. 22, 25): h^eq = rho cv T Gamma_i; the FP32 form as a deviation
+    R diff;
+    if constexpr (DEV && VR) diff = hv - fma_(rcv, fma_(G, Tfull, w * Tv), w * hoff);
+    else if constexpr (DEV) diff = fma_(-rcv, fma_(G, Tfull, w * Tv), hv);
+    else diff = fma_(-rcvT, gam, hv);
+    R hn = fma_(sh * dH(i), rcvT * gam, fma_(-wT, diff, hv));
     if (DEV) {
-      dg += eg;
-      dh += eh;
-    }
-  };
-  auto eq_f = [&](int m) {
-    return pair_eq(bf[m], fma_(0.5 * bf[m], bf[m], mh), fK0, fK1, X0[m], VR ? X1[m] : X0[m]);
-  };
-  auto Q_of = [&](int m) { return fma_(R(0.5) * b[m], b[m], mhr); };
-  auto eq_g = [&](int m, R Q) { return pair_eq(b[m], Q, gK0, gK1, XG[m], XG[m]); };
-  auto eq_h = [&](int m, R Q) { return pair_eq(b[m], Q, hK0, hK1, XH[m], XH[m]); };
-  constexpr int first[4] = {1, 2, 5, 6};   // of a pair; the opposite direction is two on
-  sink(0, 0, R(relax(fv[0], wq<double>(0), fma_(mh, fK1, fK0), omf)));
-  if constexpr (BYDIR) {
-#pragma unroll
-    for (int m0 = 0; m0 < 4; m0 += 2) {
-      PairEq<double> f[2];
-      PairEq<R> g[2], h[2];
-      R eg[2][2] = {}, eh[2][2] = {};
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int m = m0 + t;
-        const R Q = Q_of(m);
-        f[t] = eq_f(m);
-        g[t] = eq_g(m, Q);
-        h[t] = eq_h(m, Q);
-        emit_f(first[m], f[t].E + f[t].O);
-        emit_gh(first[m], g[t].E + g[t].O, h[t].E + h[t].O, eg[t][0], eh[t][0]);
-      }
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int m = m0 + t;
-        emit_f(first[m] + 2, f[t].E - f[t].O);
-        emit_gh(first[m] + 2, g[t].E - g[t].O, h[t].E - h[t].O, eg[t][1], eh[t][1]);
-        // pair by pair in either order, so that the bits are the same
-        give(eg[t][0], eh[t][0]);
-        give(eg[t][1], eh[t][1]);
+      dg += gv - gn;
+      if (kEy[i] != 0) {
+        // a move to the next row changes the reference by w rho cv Tg xi_y (not
+        // for the populations that a wall reflects)
+        const R wr = (kEy[i] > 0 ? k.wr : -k.wr) * (i < 5 ? R(4) : R(1));   // w = 4/36 or 1/36
+        const R shift = WALL && (kEy[i] > 0 ? top : bot) ? R(0) : wr;
+        hn = fma_(-shift, k.Tg, hn);
+        dh += fma_(-shift, k.Tg, hv - hn);
+      } else {
+        dh += hv - hn;
       }
     }
-  } else {
-#pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      const PairEq<double> f = eq_f(m);
-      emit_f(first[m], f.E + f.O);
-      emit_f(first[m] + 2, f.E - f.O);
-      const R Q = Q_of(m);
-      const PairEq<R> g = eq_g(m, Q), h = eq_h(m, Q);
-      R eg = 0, eh = 0;
-      emit_gh(first[m], g.E + g.O, h.E + h.O, eg, eh);
-      give(eg, eh);
-      emit_gh(first[m] + 2, g.E - g.O, h.E - h.O, eg, eh);
-      give(eg, eh);
+    if (WALL && kEy[i] != 0) {
+      const R aw = (VR && DEV) ? R(2) * w : R(2) * w * rcv;
+      hn = fma_(aw, kEy[i] > 0 ? bu : bd, (kEy[i] > 0 ? su : sd) * hn);
     }
+    sink(i, 2, hn);
   }
   // rest populations, formed in FP64
   if (DEV) {
@@ -497,15 +484,14 @@ __device__ __forceinline__ void site_collide(const StepArgs &a, int j, int x, bo
     // to its FP32 deviation.
     sink.rest(cur.g0() + double(dg), cur.h0() + double(dh));
   } else {
-    // Eqs. 12-14 as printed, term by term, g^eq_0 formed from c = sum g and the
-    // forcing added last: this value carries c, and its rounding is the one
-    // the planar Marangoni velocity is sensitive to over tens of thousands of
-    // steps (folding the forcing into the relaxation drifted from the printed
-    // form by 1.7e-10 of the velocity in 50,000 steps)
-    const double w0 = wq<double>(0), G0 = w0 * double(mhr);
-    const double geq0 = fma_(cd, G0, fma_(-(1.0 - w0), double(gmu), cd));
-    sink.rest(fma_(-double(k.omg), cur.g0() - geq0, cur.g0()) - double(k.omg * Gu) * (w0 + G0),
-              relax(cur.h0(), w0, double(fma_(mhr, hK1, hK0)), double(omT)));
+    // Eqs. 12-14 and 22 as printed: g^eq_0 = c - (1 - w0) 3 Gamma mu + c G_0
+    // with c = sum g, the forcing added last
+    const R w0 = wq<R>(0), t0 = tg(0), G0 = w0 * t0, gam0 = fma_(w0, t0, w0);
+    const R geq0 = fma_(c, G0, fma_(-(R(1) - w0), gmu, c));
+    const R g0 = R(cur.g0()), h0 = R(cur.h0());
+    const R diff0 = fma_(-rcvT, gam0, h0);
+    sink.rest(double(fma_(sg * dB(0), gam0, fma_(-k.wg, g0 - geq0, g0))),
+              double(h0 + fma_(sh * dH(0), rcvT * gam0, -(wT * diff0))));
   }
 }
 
@@ -576,14 +562,14 @@ struct RowSink {
 };
 
 // the collision and stores of a site whose wave holds row j
-template <typename S, typename R, bool DEV, int MODE, bool BYDIR>
+template <typename S, typename R, bool DEV, int MODE>
 __device__ __forceinline__ void site_update(const StepArgs &a, int j, int x, const double *cS,
                                             const double *cC, const double *cN, const R *tS,
                                             const R *tC, const R *tN, const R *pS, const R *pC,
                                             const R *pN, const RowVals<R> &cur, double *acc) {
   const bool bot = a.walls_y != 0 && j == 0, top = a.walls_y != 0 && j == a.ny - 1;
-  site_collide<R, DEV, MODE, true, BYDIR>(a, j, x, bot, top, cS, cC, cN, tS, tC, tN, pS, pC, pN, cur, acc,
-                             RowSink<S, (MODE & kStream) != 0>(a, j, x, bot, top));
+  site_collide<R, DEV, MODE, true>(a, j, x, bot, top, cS, cC, cN, tS, tC, tN, pS, pC, pN, cur, acc,
+                                   RowSink<S, (MODE & kStream) != 0>(a, j, x, bot, top));
 }
 
 // deterministic block reduction of the per-lane diagnostic sums: fixed
@@ -854,7 +840,7 @@ step_kernel(const StepArgs a) {
     }
     if (act) {
       const int l = lane;
-      site_update<S, R, DEV, MODE, true>(a, j, x, &ringc[(j - 1) & 3][l], &ringc[j & 3][l],
+      site_update<S, R, DEV, MODE>(a, j, x, &ringc[(j - 1) & 3][l], &ringc[j & 3][l],
                                    &ringc[(j + 1) & 3][l], &ringt[(j - 1) & 3][l],
                                    &ringt[j & 3][l], &ringt[(j + 1) & 3][l],
                                    &ringp[(j - 1) & 3][l], &ringp[j & 3][l],
@@ -1060,7 +1046,7 @@ small_step_kernel(const StepArgs a0, void *other, int nsteps) {
       load_site(y, x, cur);
       const size_t rS = (size_t)y * W + x, rC = rS + W, rN = rC + W;
       const bool bot = walls && y == 0, top = walls && y == ny - 1;
-      site_collide<R, DEV, MODE, true, false>(a, y, x, bot, top, lc + rS, lc + rC, lc + rN, lt + rS, lt + rC,
+      site_collide<R, DEV, MODE, true>(a, y, x, bot, top, lc + rS, lc + rC, lc + rN, lt + rS, lt + rC,
                                  lt + rN, lp + rS, lp + rC, lp + rN, cur, acc,
                                  SmallSink<S, RES>(a, RES ? ldst : static_cast<char *>(dstp), y, x,
                                                    bot, top));
@@ -1231,7 +1217,7 @@ tile_step_kernel(const StepArgs a) {
   const bool wrap = tail > 0 && tail <= 8 && (ntx == 2 || ntx == 4);
   if (y < ny && (x < nx || wrap)) {
     const int rS = ly * W + lx, rC = rS + W, rN = rC + W;
-    site_update<S, R, DEV, MODE, false>(a, y, x < nx ? x : x % nx, lc + rS, lc + rC, lc + rN,
+    site_update<S, R, DEV, MODE>(a, y, x < nx ? x : x % nx, lc + rS, lc + rC, lc + rN,
                                  lt + rS, lt + rC, lt + rN, lp + rS, lp + rC, lp + rN, cur, acc);
     if ((MODE & kDiag) && x >= nx) {
 #pragma unroll
