@@ -268,14 +268,13 @@ __device__ __forceinline__ void site_adjoint(const StepArgs &a, const Consts<R> 
 
 
 // ---- stencil transposes ---------------------------------------------------------
-// weight of neighbour direction k in the Hessian stencil of c, applied to the
-// cotangents (a_xx, a_xy, a_yy) of the site reading it: w_k (9 xi_x^2 - 3),
-// 9 w_k xi_x xi_y and w_k (9 xi_y^2 - 3)
+// weight of neighbour direction k in the Hessian stencil of c over w_k, applied
+// to the cotangents (a_xx, a_xy, a_yy) of the site reading it: 9 xi_x^2 - 3,
+// 9 xi_x xi_y and 9 xi_y^2 - 3
 template <typename R>
 __device__ __forceinline__ R hess_w(int kk, R axx, R axy, R ayy) {
-  const R wk = wq<R>(kk);
   const R ex = R(kEx[kk]), ey = R(kEy[kk]);
-  return wk * ((R(9) * ex * ex - R(3)) * axx + R(9) * ex * ey * axy + (R(9) * ey * ey - R(3)) * ayy);
+  return fma_(R(9) * ey * ey - R(3), ayy, fma_(R(9) * ex * ey, axy, (R(9) * ex * ex - R(3)) * axx));
 }
 
 
@@ -287,22 +286,33 @@ constexpr int kAdjAW = kAdjTX + 4, kAdjAH = kAdjTY + 4;
 // the site collect from the stencils that read it; the site x = y - xi_k reads
 // y through direction k.  row: the site's row (its wall is bottom for 0, top
 // for ny - 1); wall: the cell touches one.  *tw: the wall temperature's share.
+// Multiply-adds are fused where written: M reaches every population of a
+// group, so which product of a pair is rounded is part of every gradient.
 template <typename R, bool CURV>
 __device__ __forceinline__ void adj_moments(const R (*la)[kAdjAH][kAdjAW], int r, int q,
                                             bool wall, int dir, R inv_rcv, R *m, double *tw) {
+#pragma clang fp contract(off)
   R cb = 0, Tb = 0, pbv = 0;
+  auto pair = [&](int u, int v, R gx, R gy, int rr, int qq) {
+    return fma_(gx, la[u][rr][qq], gy * la[v][rr][qq]);
+  };
+  // what the cotangents at (rr, qq) give c through direction kk
+  auto to_c = [&](int kk, int rr, int qq) {
+    const R wk = wq<R>(kk), gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
+    cb += fma_(R(6) * wk, la[2][rr][qq], pair(0, 1, gx, gy, rr, qq));
+    if constexpr (CURV) cb = fma_(wk, hess_w(kk, la[7][rr][qq], la[8][rr][qq], la[9][rr][qq]), cb);
+  };
 #pragma unroll
   for (int kk = 1; kk < 9; ++kk) {
     const int rr = r - kEy[kk], qq = q - kEx[kk];
     const R wk = wq<R>(kk);
     const R gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
-    cb += gx * la[0][rr][qq] + gy * la[1][rr][qq] + R(6) * wk * la[2][rr][qq];
-    Tb += gx * la[3][rr][qq] + gy * la[4][rr][qq];
-    pbv += gx * la[5][rr][qq] + gy * la[6][rr][qq];
-    if constexpr (CURV) cb += hess_w(kk, la[7][rr][qq], la[8][rr][qq], la[9][rr][qq]);
+    to_c(kk, rr, qq);
+    Tb += pair(3, 4, gx, gy, rr, qq);
+    pbv += pair(5, 6, gx, gy, rr, qq);
   }
-  cb -= R(10.0 / 3.0) * la[2][r][q];   // centre weight of the Laplacian
-  if constexpr (CURV) cb -= R(4.0 / 3.0) * (la[7][r][q] + la[9][r][q]);   // of hxx, hyy
+  cb = fma_(-R(10.0 / 3.0), la[2][r][q], cb);   // centre weight of the Laplacian
+  if constexpr (CURV) cb = fma_(-R(4.0 / 3.0), la[7][r][q] + la[9][r][q], cb);   // of hxx, hyy
   *tw = 0.0;
   // wall rows: a site x of the same row whose stencil direction k points into
   // the ghost row reads the mirror image of x + xi_k, which is y
@@ -314,12 +324,11 @@ __device__ __forceinline__ void adj_moments(const R (*la)[kAdjAH][kAdjAW], int r
       const int qq = q - kEx[kk];
       const R wk = wq<R>(kk);
       const R gx = R(3) * wk * R(kEx[kk]), gy = R(3) * wk * R(kEy[kk]);
-      cb += gx * la[0][r][qq] + gy * la[1][r][qq] + R(6) * wk * la[2][r][qq];
-      if constexpr (CURV) cb += hess_w(kk, la[7][r][qq], la[8][r][qq], la[9][r][qq]);
-      pbv += gx * la[5][r][qq] + gy * la[6][r][qq];
-      const R tg = gx * la[3][r][qq] + gy * la[4][r][qq];
+      to_c(kk, r, qq);
+      pbv += pair(5, 6, gx, gy, r, qq);
+      const R tg = pair(3, 4, gx, gy, r, qq);
       Tb -= tg;
-      twb += 2.0 * double(tg);
+      twb = fma_(2.0, double(tg), twb);
     }
     *tw = twb;
   }
@@ -471,12 +480,15 @@ adj_step_kernel(const AdjArgs aa) {
       const R lh = lam[18 + i] + lm[2][r][q];
       if (out) {
         lam[18 + i] = -lh;
-        tw_acc += 2.0 * double(wq<R>(i)) * a.rcv * double(lh);
+        tw_acc = fma_(2.0 * double(wq<R>(i)) * a.rcv, double(lh), tw_acc);
       } else {
         lam[18 + i] = lh;
       }
     }
-    if (bot || top) aa.dtw[(bot ? 0 : nx) + x] += tw_acc + ltw[bot ? 0 : 1][lx];
+    if (bot || top) {   // in the order of the steps
+      double *dtw = aa.dtw + (bot ? 0 : nx) + x;
+      *dtw = (*dtw + ltw[bot ? 0 : 1][lx]) + tw_acc;
+    }
     // linearisation point and stencils, as in the forward step
     const int cx = lx + 1, cy = ly + 1;
     const double cd = lc[cy][cx];

@@ -1,13 +1,13 @@
-"""The bits of states and diagnostics, against stored ones.
+"""The bits of states, diagnostics and gradients, against stored ones.
 
 The droplet velocity u_r = sum c u_y / sum c of a short run is the residue of a
 sum that cancels over several orders of magnitude, so it carries the rounding
 of every population: two evaluations of one collision that agree to FP32
 rounding in the fields differ by up to 1e-2 of u_r.  A kernel that takes over a
 grid, or a cheaper form of the collision, must therefore leave every bit of the
-state as it was.  tests/golden/state_bits.json holds digests of the states and
-the diagnostic sums that the library of commit 5897d12 (one launch a step) gives
-for the runs below.
+state as it was.  tests/golden/state_bits.json holds digests of the states, the
+diagnostic sums and the gradients that the library of commit 5897d12 (one
+launch a step, moments replayed in the backward pass) gives for the runs below.
 
     PYTHONPATH=<checkout> python tests/test_gpu_state_bits.py > tests/golden/state_bits.json
 
@@ -41,6 +41,11 @@ RUNS = [
     (130, 41, 1, dict(CONST, rho2=2.0, csf_form=1)),
     (1200, 1030, 1, dict(CONST, **LINEAR)), (1230, 1003, 1, dict(VARY, csf_form=1)),
     (1200, 1030, 1, dict(CONST, rho2=2.0, **LINEAR)), (2048, 800, 1, dict(CONST, **LINEAR)),
+]
+GRADS = [
+    (130, 40, 1, CONST, 16), (70, 33, 0, VARY, 9), (20, 17, 1, dict(CONST, csf_form=1), 16),
+    (300, 200, 1, dict(VARY, csf_form=1), 5), (300, 200, 1, CONST, 12),
+    (1200, 1030, 1, dict(CONST, **LINEAR), 4),
 ]
 PRECISIONS = ("fp64", "fp32_dev")
 
@@ -98,6 +103,17 @@ def _run(lbe, nx, ny, walls, over, precision):
     return out, cuy
 
 
+def _grad(lbe, nx, ny, walls, over, steps, precision):
+    import torch
+    p, phi, T0, tb, tt = _case(nx, ny, walls, over)
+    sim = lbe.Simulation(p, phi, T0, tb, tt, precision=precision, record_steps=steps)
+    sim.step(steps, record=True)
+    seed = np.random.default_rng(steps).random((ny, nx)) - 0.5
+    g = sim.backward(torch.as_tensor(seed), want_F0=True, want_T0=True)
+    torch.cuda.synchronize()
+    return dict(sigmaT=float(g["sigmaT"]).hex(), **{k: _digest(g[k]) for k in ("Twall", "F0", "T0")})
+
+
 @pytest.fixture(scope="module")
 def lbe():
     import torch
@@ -136,8 +152,17 @@ def test_states_and_diagnostics(lbe, golden, run, precision):
     assert got["twelve"] == ref["twelve"], key
 
 
+@pytest.mark.parametrize("precision", PRECISIONS)
+@pytest.mark.parametrize("case", GRADS, ids=lambda c: f"{c[0]}x{c[1]}-{c[4]}")
+def test_gradients(lbe, golden, case, precision):
+    key = _key(*case[:4], precision, case[4])
+    print(f"case {key}", flush=True)
+    assert _grad(lbe, *case, precision) == golden["grads"][key], key
+
+
 if __name__ == "__main__":
     from paper_1412_6238_amd import lbe_csf as L
     print(f"library: {L.LIB_PATH}", file=sys.stderr, flush=True)
-    out = dict(runs={_key(*r, p): _run(L, *r, p)[0] for r in RUNS for p in PRECISIONS})
+    out = dict(runs={_key(*r, p): _run(L, *r, p)[0] for r in RUNS for p in PRECISIONS},
+               grads={_key(*c[:4], p, c[4]): _grad(L, *c, p) for c in GRADS for p in PRECISIONS})
     json.dump(out, sys.stdout, indent=1)
