@@ -187,17 +187,7 @@ void launch_mode(const Launch &la, const StepArgs &a, hipStream_t st) {
     switch (la.pipe) {
       case 0: launch_pipe<S, R, DEV, MODE, 0>(la, a, st); break;
       case 2: launch_pipe<S, R, DEV, MODE, 2>(la, a, st); break;
-      default:
-        // FP64, one block per CU: a wave alone on its SIMD would wait for its
-        // stores before the next row's loads (memory operations complete in
-        // order), so there the loads are issued before the stores, as with two
-        // rows ahead: 4096^2 1385 against 1775 us a step, 2048^2 362 against 441 (not
-        // for the fields, which store little: 213 us one ahead, 229 two)
-        if (sizeof(S) == 8 && !(MODE & kFields) && la.nw == 4 && la.nblocks <= kNumCUs)
-          launch_pipe<S, R, DEV, MODE, 2>(la, a, st);
-        else
-          launch_pipe<S, R, DEV, MODE, 1>(la, a, st);
-        break;
+      default: launch_pipe<S, R, DEV, MODE, 1>(la, a, st); break;
     }
   }
 }

@@ -1,0 +1,48 @@
+"""Which kernels a handle's steps run: the names that torch's profiler records.
+
+A wrong route gives the right numbers (all kernels give the same bits), so only
+the names show that an override, or a rule on the grid, was followed."""
+import re
+
+import pytest
+
+from paper_1412_6238_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lbe():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1412_6238_amd import lbe_csf
+    return lbe_csf
+
+
+def kernels(lbe, nx, ny, precision, steps, **kw):
+    """Short names of the library's kernels of sim.step(steps), in order."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    case = wl.random_case(nx, ny, seed=nx + ny, **kw)
+    sim = lbe.Simulation(case["params"], case["phi0"], case["T0"], case["Twall_bot"],
+                         case["Twall_top"], precision=precision)
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA, ProfilerActivity.CPU]) as prof:
+        sim.step(steps)
+        torch.cuda.synchronize()
+    events = sorted((e for e in prof.events() if "lbe::" in e.name), key=lambda e: e.time_range.start)
+    names = [re.search(r"lbe::(\w+)(<[^(]*>)?", e.name) for e in events]
+    return [(m[1], [v.strip() for v in (m[2] or "<>")[1:-1].split(",")]) for m in names]
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_dev"])
+@pytest.mark.parametrize("pipe", ["0", "1", "2"])
+def test_row_pipeline_override(lbe, monkeypatch, pipe, precision):
+    """LBE_CSF_PIPE asks for a row pipeline and gets it (136 x 40, blocks of
+    four waves in FP64: the shape that tests/test_gpu_parity.py compares)."""
+    monkeypatch.setenv("LBE_CSF_TILE", "0")
+    monkeypatch.setenv("LBE_CSF_PIPE", pipe)
+    monkeypatch.setenv("LBE_CSF_ROWS", "7")
+    ks = kernels(lbe, 136, 40, precision, 2)
+    assert [k[0] for k in ks] == ["step_kernel"] * 2, ks
+    assert all(k[1][-1] == pipe for k in ks), ks   # the last parameter is the pipeline
