@@ -137,16 +137,20 @@ typedef struct lbe_csf lbe_csf; /* opaque host object */
 
 /* Bytes of device workspace needed for these parameters.  record_steps > 0
  * reserves room for lbe_csf_backward after a recorded run of that many steps
- * (ceil(sqrt(N)) spaced checkpoints plus one segment of replay states and,
- * with constant relaxation times, the moments that the run tapes itself, up to
- * 48 GiB while the total stays within 64 GiB).
+ * (ceil(sqrt(N)) spaced checkpoints plus one segment of replay states).
+ * This is the least that lbe_csf_create takes.  With constant relaxation times
+ * a workspace with more saves recomputation: each further
+ * nx*ny*(8 + 4 value bytes), rounded up to 256, holds the moments of one more
+ * of the last steps, and lbe_csf_workspace_size(params, 1, .) plus N of them
+ * those of the whole run.  Gradients do not depend on it.
  * Two densities add one FP64 plane of nx*ny (the pressure of Eq. 9).
  * Errors: EINVAL for invalid parameters or NULL bytes. */
 LBE_CSF_API int lbe_csf_workspace_size(const lbe_csf_params *params, int64_t record_steps,
                            size_t *bytes);
 
 /* Create a handle and write F_0 (the equilibrium of the initial fields).
- * workspace: device memory of at least workspace_size bytes, 256-byte aligned.
+ * workspace: device memory of at least workspace_size bytes, 256-byte aligned;
+ * bytes: its size.
  * stream: hipStream_t the handle enqueues on.
  * phi0, T0: device FP64 arrays of nx*ny (phi = 2c - 1, c = 1 in fluid 2).
  * Twall_bot, Twall_top: device FP64 arrays of nx, the wall temperatures at

@@ -104,20 +104,8 @@ struct AdjLayout {
   size_t off_out;         // FP64 scalar result
   size_t off_direct;      // moment sets that the recorded run writes itself
   int64_t direct;         // ... of this many last steps
-  size_t off_a2;          // a second set of stencil cotangents
   size_t total;
 };
-// Bytes of moment sets that a recorded run writes as it goes, instead of
-// leaving them to a replay in the backward pass: at most 48 GiB of the 288 GB,
-// and only what keeps the adjoint region within 64 GiB (a record that needs
-// more than that without them is laid out as if there were none).  That is all
-// of 4,000 steps of 256 x 512 in FP32 (12.6 GB) and most of 400 steps of
-// 4096 x 1024.  Taping costs the forward step 24 bytes a site, the replay costs
-// the whole step again.  Measured, forward and backward of 40 steps of
-// 4096 x 1024 and of 200 of 256 x 512, with the one-kernel adjoint step:
-// 27.1 -> 17.8 ms and 6.4 -> 4.9 ms.
-constexpr size_t kDirectTape = size_t(48) << 30, kDirectTotal = size_t(64) << 30;
-
 inline int64_t adj_segment_length(int64_t nsteps) {
   if (nsteps <= 1) return 1;
   int64_t K = (int64_t)std::ceil(std::sqrt((double)nsteps));
@@ -130,7 +118,7 @@ inline int adj_tiles_x(int nx) { return (nx + kAdjTX - 1) / kAdjTX; }
 inline int adj_tiles_y(int ny) { return (ny + kAdjTY - 1) / kAdjTY; }
 
 inline AdjLayout adj_layout(int nx, int ny, size_t state_bytes, size_t value_bytes,
-                            int64_t record_steps, bool direct) {
+                            int64_t record_steps) {
   AdjLayout A{};
   auto al = [](size_t v) { return (v + 255) / 256 * 256; };
   A.record_steps = record_steps;
@@ -149,14 +137,37 @@ inline AdjLayout adj_layout(int nx, int ny, size_t state_bytes, size_t value_byt
   A.off_part = o; o += al((size_t)adj_tiles_x(nx) * adj_tiles_y(ny) * sizeof(double));
   A.off_tw = o; o += al(2 * (size_t)nx * sizeof(double));
   A.off_out = o; o += 256;
-  const size_t room = o < kDirectTotal ? std::min(kDirectTape, kDirectTotal - o) : 0;
-  A.direct = direct ? std::min<int64_t>(record_steps, (int64_t)(room / A.mom_bytes)) : 0;
-  if (const char *e = std::getenv("LBE_CSF_DIRECT"))   // at most this many steps
-    A.direct = std::min<int64_t>(A.direct, std::max(0, std::atoi(e)));
-  A.off_direct = o; o += (size_t)A.direct * A.mom_bytes;
-  A.off_a2 = o; o += kAdjA * A.plane_bytes;
   A.total = o;
   return A;
+}
+
+// Places the moment sets that a recorded run writes as it goes, instead of
+// leaving them to a replay in the backward pass, in the bytes that the region
+// has.  Where the sets of all steps fit, nothing is replayed and they take the
+// place of checkpoints and replay tapes: that is without a byte more up to some
+// 150 steps.  Otherwise the last steps are taped in what lies beyond the
+// region's own size.  Taping costs the forward step 24 bytes a site in FP32,
+// the replay costs the whole step again: forward and backward of 40 steps of
+// 4096 x 1024 27.1 -> 18.2 ms, of 200 of 256 x 512 6.4 -> 5.0 ms.
+// LBE_CSF_DIRECT limits the number of steps.
+inline void adj_place_tape(AdjLayout &A, size_t avail) {
+  int64_t limit = A.record_steps;
+  if (const char *e = std::getenv("LBE_CSF_DIRECT"))
+    limit = std::min<int64_t>(limit, std::max(0, std::atoi(e)));
+  if (limit <= 0 || avail < A.total) return;
+  // (steps by division: their product with the set size could overflow)
+  const bool all = limit == A.record_steps && (size_t)limit <= avail / A.mom_bytes;
+  const size_t sets = all ? (size_t)limit * A.mom_bytes : 0;
+  const size_t shift = sets > A.off_lam ? sets - A.off_lam : 0;
+  if (all && shift <= avail - A.total) {
+    A.off_direct = 0;
+    A.direct = limit;
+    for (size_t *off : {&A.off_lam, &A.off_part, &A.off_tw, &A.off_out, &A.total}) *off += shift;
+  } else {
+    A.off_direct = A.total;
+    A.direct = std::min<int64_t>(limit, (int64_t)((avail - A.total) / A.mom_bytes));
+    A.total += (size_t)A.direct * A.mom_bytes;
+  }
 }
 
 namespace host {
@@ -436,7 +447,9 @@ inline bool params_valid(const lbe_csf_params *p, std::string *why) {
   return true;
 }
 
-inline Layout make_layout(const lbe_csf_params *p, int64_t record_steps) {
+// bytes: of the workspace at hand; what it has beyond the least holds a moment
+// tape (0: the least itself, without a tape)
+inline Layout make_layout(const lbe_csf_params *p, int64_t record_steps, size_t bytes = 0) {
   Layout L{};
   const size_t n = (size_t)p->nx * p->ny;
   const size_t vb = p->precision == LBE_CSF_FP64 ? 8 : 4;
@@ -460,9 +473,10 @@ inline Layout make_layout(const lbe_csf_params *p, int64_t record_steps) {
   L.off_rec = o; o = align_up(o + sizeof(DiagRecord));
   L.off_pc = o; o = align_up(o + (two_densities(p) ? n * 8 : 0));   // pressure of Eq. 9
   L.off_adj = o;
+  L.adj = adj_layout(p->nx, p->ny, L.state_bytes, vb, record_steps);
   // constant relaxation times need the moments only, so these can be taped
-  const bool constant = p->tau_f[0] == p->tau_f[1] && p->tau_T[0] == p->tau_T[1];
-  L.adj = adj_layout(p->nx, p->ny, L.state_bytes, vb, record_steps, constant);
+  if (p->tau_f[0] == p->tau_f[1] && p->tau_T[0] == p->tau_T[1] && bytes > o)
+    adj_place_tape(L.adj, bytes - o);
   o = align_up(o + L.adj.total);
   L.total = o;
   return L;

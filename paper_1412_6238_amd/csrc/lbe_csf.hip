@@ -511,7 +511,9 @@ int run_backward(lbe_csf *h, const double *dJdc, double *dsT, double *dTw, doubl
   const size_t pl = A.plane_bytes;
   void *D[2] = {lam, lam + 27 * pl};
   void *M0 = lam + 54 * pl;
-  void *Abuf[2] = {lam + 60 * pl, base + A.off_a2};
+  // the second set of stencil cotangents takes the state buffer that the next
+  // step writes whole
+  void *Abuf[2] = {lam + 60 * pl, h->state[1 - h->cur]};
   const bool curv = h->P.csf_form == 1;
   const int na = curv ? kAdjA : 7;
   double *part = reinterpret_cast<double *>(base + A.off_part);
@@ -750,10 +752,11 @@ int lbe_csf_create(const lbe_csf_params *params, void *workspace, size_t bytes,
   if (record_steps < 0) return fail(nullptr, LBE_CSF_EINVAL, "record_steps < 0");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign)
     return fail(nullptr, LBE_CSF_EINVAL, "workspace not 256-byte aligned");
-  const Layout L = make_layout(params, record_steps);
+  Layout L = make_layout(params, record_steps);
   if (bytes < L.total)
     return fail(nullptr, LBE_CSF_ENOMEM,
                 "workspace too small: need " + std::to_string(L.total) + " bytes");
+  L = make_layout(params, record_steps, bytes / kAlign * kAlign);
   lbe_csf *h = new (std::nothrow) lbe_csf();
   if (!h) return fail(nullptr, LBE_CSF_ENOMEM, "host allocation failed");
   h->P = *params;

@@ -139,6 +139,35 @@ def workspace_bytes(params: lbe_csf_params, record_steps: int = 0) -> int:
     return n.value
 
 
+# A record takes at most this share of the free device memory for moments that
+# the run tapes itself (beyond what its workspace needs), so that any number of
+# live records leaves most of it to their program.
+TAPE_SHARE = 32
+# Less than this is taken without a look at the free memory, which costs 0.2 ms.
+TAPE_SMALL = 256 << 20
+
+
+def _tape_bytes(params: lbe_csf_params, record_steps: int, device) -> int:
+    """Bytes beyond workspace_bytes that hold moments of the run's last steps:
+    those of all of them, as far as the share of the free memory goes."""
+    import torch
+    if record_steps <= 0 or params.tau_f[0] != params.tau_f[1] or params.tau_T[0] != params.tau_T[1]:
+        return 0
+    value = 8 if params.precision == LBE_CSF_FP64 else 4
+    one = -(-params.nx * params.ny * (8 + 4 * value) // 256) * 256
+    least = workspace_bytes(params, record_steps)
+    limit = os.environ.get("LBE_CSF_DIRECT")
+    if limit is not None and int(limit) < record_steps:
+        want = max(0, int(limit)) * one
+    else:
+        want = workspace_bytes(params, 1) + record_steps * one - least
+    if want <= TAPE_SMALL:
+        return max(0, want)
+    free = torch.cuda.mem_get_info(device)[0]
+    free += torch.cuda.memory_reserved(device) - torch.cuda.memory_allocated(device)
+    return min(want, free // TAPE_SHARE)
+
+
 def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
@@ -161,8 +190,16 @@ class Simulation:
         self.record_steps = int(record_steps)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         nbytes = workspace_bytes(self.P, self.record_steps)
+        extra = _tape_bytes(self.P, self.record_steps, self.device)
         with torch.cuda.device(self.device):
-            self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            try:
+                self.workspace = torch.empty(nbytes + extra, dtype=torch.uint8, device=self.device)
+            except torch.cuda.OutOfMemoryError:
+                if not extra:
+                    raise
+                # the least that works: segments without a tape are replayed
+                self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
+            nbytes = self.workspace.numel()
         dev = lambda a: None if a is None else torch.as_tensor(
             np.ascontiguousarray(a) if isinstance(a, np.ndarray) else a,
             dtype=torch.float64).to(self.device).contiguous()
