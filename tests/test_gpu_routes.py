@@ -46,3 +46,34 @@ def test_row_pipeline_override(lbe, monkeypatch, pipe, precision):
     ks = kernels(lbe, 136, 40, precision, 2)
     assert [k[0] for k in ks] == ["step_kernel"] * 2, ks
     assert all(k[1][-1] == pipe for k in ks), ks   # the last parameter is the pipeline
+
+
+@pytest.mark.parametrize("precision,nw,want", [("fp32_dev", "1", "1"), ("fp32_dev", "8", "8"),
+                                               ("fp64", "8", "2")])
+def test_pair_block_override(lbe, monkeypatch, precision, nw, want):
+    """LBE_CSF_PAIR_NW picks the blocks that tests/test_gpu_pair_variants.py
+    compares (FP64 has one kind)."""
+    monkeypatch.setenv("LBE_CSF_PAIR", "1")
+    monkeypatch.setenv("LBE_CSF_PAIR_NW", nw)
+    ks = kernels(lbe, 500, 33, precision, 4)
+    assert [k[0] for k in ks] == ["pair_step_kernel"] * 2, ks
+    assert all(k[1][-1] == want for k in ks), ks   # the last parameter: waves a block
+
+
+@pytest.mark.parametrize("nx,ny,precision,rho2,want", [
+    (16, 16, "fp64", 0, ["small_step_kernel"]),
+    (8, 64, "fp64", 0, ["pair_tile_kernel"] * 2), (160, 300, "fp32_dev", 0, ["pair_tile_kernel"] * 2),
+    (8, 4096, "fp32_dev", 0, ["tile_step_kernel"] * 4),
+    (256, 512, "fp32_dev", 0, ["tile_step_kernel"] * 4),
+    (720, 720, "fp64", 0, ["pair_step_kernel"] * 2),
+    (1160, 1020, "fp32_dev", 0, ["tile_step_kernel"] * 4),
+    (1200, 1030, "fp32_dev", 0, ["pair_step_kernel"] * 2),
+    (1200, 1030, "fp32_dev", 2.0, ["tile_step_kernel"] * 8),
+    (1300, 1100, "fp32_dev", 2.0, ["density_step_kernel"] * 4),
+    (720, 720, "fp64", 2.0, ["density_step_kernel"] * 4)])
+def test_default_routes(lbe, monkeypatch, nx, ny, precision, rho2, want):
+    """Four plain steps on grids at both sides of each rule."""
+    for v in ("PAIR", "PAIR_NW", "PAIR_ROWS", "NW", "ROWS", "PIPE", "STREAM", "TILE", "SMALL"):
+        monkeypatch.delenv("LBE_CSF_" + v, raising=False)
+    ks = kernels(lbe, nx, ny, precision, 4, **(dict(rho2=rho2) if rho2 else {}))
+    assert [k[0] for k in ks] == want, ks
