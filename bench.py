@@ -31,13 +31,6 @@ BYTES_PER_SITE = {"fp32_dev": 216, "fp64": 432}
 # bytes the state layout actually moves per pass: the FP32 form keeps
 # the rest population g_0 in FP64, 2 x (26 x 4 + 8) = 224
 STORED_BYTES_PER_SITE = {"fp32_dev": 224, "fp64": 432}
-# steps that one pass over the state takes: two in one launch on grids whose
-# state does not stay in the caches (pair_launch in host_layout.h), so a step
-# reads and writes half of the above
-PAIRED_SITES = {"fp32_dev": 1_100_000, "fp64": 500_000}
-# two densities: the state is read once from these sizes on (density_launch),
-# and half again by a pressure pass below
-ONE_LAUNCH_SITES = {"fp32_dev": 700_000, "fp64": 500_000}
 REPEATS = 5
 # the step kernel and its launch shape and store policy (host_layout.h)
 KERNEL_SOURCES = ("paper_1412_6238_amd/csrc/step_kernel.h", "paper_1412_6238_amd/csrc/pair_kernel.h",
@@ -73,6 +66,30 @@ def traffic_from_profile(workload, precision, sites, csf_form=0):
     if d.get("kernel_hash") != kernel_hash():
         return None
     return d["bytes_per_launch"] / d.get("steps_per_launch", 1)   # of one step
+
+
+def passes_per_step(torch, sim, steps=8):
+    """What `steps` steps of a handle read and write, from the kernels that they
+    launch (torch's profiler): (passes over the state, pressure passes) per
+    step, or None where the profiler records no kernel.  Two steps in one launch
+    are one pass; with two densities as two launches the pressure pass reads
+    the state once more."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
+        sim.step(steps)
+        torch.cuda.synchronize()
+    stored = pressure = 0
+    for e in prof.events():
+        m = re.search(r"lbe::(small_step|step|tile_step|pair_step|pair_tile|density_step)_kernel<([^(]*)>",
+                      e.name)
+        if not m:
+            continue
+        if m[1] == "small_step":   # many steps a launch, one pass over memory each
+            return 1.0, 0.0
+        mode = int(m[2].split(",")[3])
+        pressure += bool(mode & 64)   # kPress
+        stored += mode & 1            # kStore
+    return (stored / steps, pressure / steps) if stored else None
 
 
 def _oracle_band_mlups(w, rows, seconds, threads=None):
@@ -310,18 +327,19 @@ def main():
     # reduction launch per diagnostic step
     bps = BYTES_PER_SITE[args.precision]
     stored = STORED_BYTES_PER_SITE[args.precision]
-    per_pass = 1
-    if args.rho2 > 0:
-        if sites < ONE_LAUNCH_SITES[args.precision]:
-            # two launches: the pressure pass reads the 27 values (half the
-            # step's bytes) and writes the FP64 pressure of Eq. 9 (8 B), which
-            # the step then reads (8 B)
-            bps += bps // 2 + 8 + 8
-            stored += stored // 2 + 8 + 8
-    elif sites >= PAIRED_SITES[args.precision]:
-        per_pass = 2
-        bps //= 2
-        stored //= 2
+    # what a step of this workload reads and writes, from a handle of its own
+    # (the timed one keeps its step count)
+    probe = lbe_csf.Simulation(p, w["phi0"], w["T0"], w["Twall_bot"], w["Twall_top"],
+                               precision=args.precision, diag_every=args.diag_every)
+    passes = passes_per_step(torch, probe)
+    del probe
+    stored_passes, pressure_passes = passes or (1.0, 0.0)
+    # a pressure pass reads the 27 values and writes the FP64 pressure of Eq. 9,
+    # which the step then reads
+    per_step = lambda b: b * stored_passes + (b / 2 + 8 + 8) * pressure_passes
+    whole = lambda v: int(v) if v == int(v) else round(v, 2)
+    bps, stored = whole(per_step(bps)), whole(per_step(stored))
+    per_pass = whole(1.0 / stored_passes) if passes else None
     achieved = bps * sites / (ms_per_step / 1e3) / 1e9
     traffic = (traffic_from_profile(args.workload, args.precision, sites, args.csf_form)
                if args.rho2 <= 0 else None)
