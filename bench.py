@@ -71,9 +71,12 @@ def traffic_from_profile(workload, precision, sites, csf_form=0):
 def passes_per_step(torch, sim, steps=8):
     """What `steps` steps of a handle read and write, from the kernels that they
     launch (torch's profiler): (passes over the state, pressure passes) per
-    step, or None where the profiler records no kernel.  Two steps in one launch
-    are one pass; with two densities as two launches the pressure pass reads
-    the state once more."""
+    step, or None where the profiler records no kernel or this program already
+    runs under rocprofv3 (one profiler at a time; its variables say so).  Two
+    steps in one launch are one pass; with two densities as two launches the
+    pressure pass reads the state once more."""
+    if any(k.startswith(("ROCPROF_", "ROCP_")) for k in os.environ):
+        return None
     from torch.profiler import ProfilerActivity, profile
     with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
         sim.step(steps)

@@ -94,7 +94,7 @@ struct Consts {
 // cotangents of the stencil values (gcx, gcy, lapc, gTx, gTy, gpx, gpy, and
 // with CURV the Hessian hxx, hxy, hyy of the curvature form), which the
 // stencil transpose hands on to the neighbours' moments; and
-// *dsT += dJ/dsigmaT.  The arithmetic differentiated is site_update's.  With
+// *dsT += dJ/dsigmaT.  The arithmetic differentiated is site_collide's.  With
 // constant relaxation times the populations enter the collision only through
 // the moments, so the moments suffice.
 template <typename R, bool DEV, bool VARTAU, bool CURV>

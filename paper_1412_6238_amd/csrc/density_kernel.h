@@ -14,8 +14,9 @@ namespace lbe {
 // own sites.  At row r it loads row r + 2, forms the moments of row r + 1, the
 // pressure of row r and the collision of row r - 1; the loads come before the
 // collision's stores, which they would otherwise wait for.  Four rows stay in
-// registers, so a CU holds four waves.  The arithmetic is that of the two launches (site_moments, site_collide with
-// kPress and with kStore), so the states are bitwise the same.
+// registers, so a CU holds four waves.  The arithmetic is that of the two
+// launches (site_moments, site_collide with kPress and with kStore), so the
+// states are bitwise the same.
 using host::kDensityHalo;
 
 template <typename R>

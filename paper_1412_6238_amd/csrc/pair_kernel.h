@@ -15,9 +15,10 @@ namespace lbe {
 //
 // A wave owns kPairCols columns (one lane each, of which the outer four on
 // each side only feed the others: a step's cone is two sites wide) and
-// marches up a chunk of rows, independent of every other wave: no barriers,
-// the exchange between its lanes goes through its own piece of LDS.  At row r
-// it
+// marches up a chunk of rows.  It shares no data with other waves: the exchange
+// between its lanes goes through its own piece of LDS.  Where a block has more
+// than one wave (neighbouring strips) they meet at a barrier once a row, only to
+// keep the strips in step.  At row r a wave
 //   - forms the moments of row r + 1 of F_n (loaded one iteration earlier),
 //   - collides row r of F_n and streams it into LDS,
 //   - loads row r + 2,
@@ -30,9 +31,10 @@ namespace lbe {
 //
 // LDS of a wave: the moments of three rows at both times, and of F_{n+1} the
 // populations that a later row collects: those moving up of three rows, those
-// moving along x of two, those moving down and sideways of one (the others
-// stay in registers).  18.2 KB in the FP32 form (eight waves a CU), 33.3 KB
-// in FP64 (four).
+// moving along x of two, those moving down and sideways of one, and those that
+// stay in their column (at rest, straight down) of one and of three.  20,008
+// bytes in the FP32 form (eight waves a CU, with under 4 KB of its 160 KB
+// left), 36,336 in FP64 (four).
 using host::kPairHalo;
 
 template <typename S, typename R>
@@ -48,6 +50,8 @@ struct PairLds {
   typename RestRaw<rest_fmt<S>(1)>::T h0[64];
   S f0[64], south[3][64];
 };
+static_assert(8 * sizeof(PairLds<float, float>) <= 160 * 1024);
+static_assert(4 * sizeof(PairLds<double, double>) <= 160 * 1024);
 
 // A scalar that the compiler recomputes from: multiples of the plane stride
 // kept for a whole loop would take all scalar registers and spill to lanes of

@@ -252,7 +252,8 @@ __device__ __forceinline__ double quotient(double a, double b, double inv) {
 // residue of a sum that cancels over five orders of magnitude, and carries the
 // rounding of every FP32 population (1e-3 of it after one step from a droplet
 // at rest).  An evaluation by even and odd parts of opposite directions, with
-// the forcing folded into the equilibrium, takes a fifth fewer instructions;
+// the forcing folded into the equilibrium, takes a quarter fewer instructions
+// (447 vector instructions a site and step in the FP32 pair kernel, 600 here);
 // it is as exact in the fields but not the same in u_r, and its FP64 error
 // against 64-bit evaluations of the printed form is 1.2 to 1.7 times as large.
 //
@@ -1101,6 +1102,10 @@ small_step_kernel(const StepArgs a0, void *other, int nsteps) {
 // Every mode of step_kernel but the streaming-store policy (diagnostics: one
 // FP64 partial per block, as there); with two densities the pressure pass
 // and the step, whose cells take p from the pressure plane as the ring does.
+// Below some 200k sites a launch is one wave's latency; above, waves in
+// flight.  The FP64 form with one density takes 147 registers, three waves a
+// SIMD (700 x 640 31.0 us, 512 x 1024 35.4); held to the 128 of four it spills
+// (512 x 1024 43).
 template <typename S, typename R, bool DEV, int MODE>
 __global__ void __launch_bounds__(kTileX * kTileY)
 tile_step_kernel(const StepArgs a) {
