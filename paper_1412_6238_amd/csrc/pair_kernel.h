@@ -522,7 +522,7 @@ pair_tile_kernel(const StepArgs a) {
       if (q != 9 && q != 18) cur.v[q] = R(buf_load<S>(rsrc, vx, ro + (uint32_t)plane_of(q) * pb));
     cur.g0r = buf_load<T0>(rsrc, (uint32_t)x * (uint32_t)sizeof(T0), ro + rb0);
     cur.h0r = buf_load<T1>(rsrc, (uint32_t)x * (uint32_t)sizeof(T1), ro + rb1);
-    if (sizeof(S) == 4) touch_args(a);   // FP32 3.63 -> 3.33 us a step on 40 x 100; FP64 no gain
+    if (sizeof(S) == 4) touch_args(a);   // FP32 3.78 -> 3.53 us a step on 40 x 100; FP64 no gain
     put(cur);
   }
   // FP32: a wave takes the form with walls only where its own row touches one
