@@ -272,22 +272,30 @@ inline bool two_densities(const lbe_csf_params *p) { return p->rho2 > 0.0 && p->
 // Two plain steps per launch (pair_step_kernel): strips of columns and chunks
 // of rows, one wave each; rows = 0 where the steps go one by one.
 //
-// Taken where a state no longer fits the caches, or close to it: FP32 from
-// 1.2M sites, FP64 from half a million (one density).  Measured on MI355X
-// against one launch per step, interleaved windows, us per step, FP32: 4096^2
-// 690 -> 456, 4096 x 1024 182 -> 131, 1500^2 116 -> 84, 1200^2 80 -> 59,
-// 1200 x 1020 62 -> 52, and below the line, where two states (224 B a site)
-// still fit the 256 MB last-level cache, 1160 x 1020 40 -> 49, 1024^2 35 -> 44,
-// 512 x 1024 20 -> 34; FP64: 4096^2 1380 -> 698, 2048^2 358 -> 198, 1030 x 777
-// 80 -> 55, 800^2 60 -> 43, at the line 512 x 1024 35.4 -> 35.5, below it
-// 256 x 512 11.5 -> 23.  (The chunks of a small grid are short against the eight
-// rows that their cones add.)
+// Taken where two states no longer fit the 256 MB last-level cache, or close to
+// it (pairs_pay).  Measured on MI355X against one launch per step, us per step,
+// FP32: 4096^2 690 -> 456, 4096 x 1024 182 -> 131, 1500^2 116 -> 84, 1200^2 80
+// -> 59, 1024 x 1290 72 -> 58, and below the line, where two states (224 B a
+// site) still fit, 1024 x 1172 45 -> 53, 1024^2 35 -> 44, 512 x 1024 20 -> 34;
+// FP64: 4096^2 1380 -> 698, 2048^2 358 -> 198, 1030 x 777 80 -> 55, 800^2 60 ->
+// 43, 1024 x 645 74 -> 45, below it 256 x 512 11.5 -> 23.  (The chunks of a
+// small grid are short against the eight rows that their cones add.)  Between
+// 2^19 and 650k sites in FP64 it depends on the columns that the strips leave
+// idle and on what a step alone takes: 743 x 781 39.6 -> 37.0 and 512 x 1036,
+// on the row-marching kernel, 51 -> 36, but 130 x 4462 41.4 -> 43.6, 300 x 1767
+// 35.8 -> 36.9; from half a million 4000 x 126 41 -> 34.  A width that needs
+// twice the waves of a step's tiles waits for the step to get slower: FP32 60 x
+// 22001 66 -> 73, 60 x 25834 101 -> 86; FP64, where one strip is cut in two for
+// its block, 23 x 28696 90 -> 99, 9 x 73334 169 -> 219, 23 x 86533 832 -> 269.
 //
 // A block's waves take neighbouring strips and march in step, so that the
 // lines at their seams are read and written by one CU at one time.  Eight FP32
 // waves a block against one: 4096^2 456 against 560, 4096 x 1024 131 against
 // 144; on smaller grids, which fit such blocks less evenly, one is faster:
-// 2048 x 1024 78 against 82, 1200^2 59 against 63.  FP64 blocks have two waves
+// 2048 x 1024 78 against 82, 1200^2 59 against 63; and on widths that fill them
+// badly: 500 x 16001 (nine strips) 344 against 280, 254 x 12008 (five) 143
+// against 125, 52 x 58654 (one, cut in eight) 537 against 126 and 220 one by
+// one, but 400 x 7626 (eight) 111 against 121.  FP64 blocks have two waves
 // (four: 4096^2 728 against 698, 1200^2 90 against 84).  One block more than are
 // resident at once would run alone, so the chunks are as many as fit (FP32
 // eight waves a CU, FP64 four, by registers and LDS).
@@ -296,9 +304,13 @@ inline bool two_densities(const lbe_csf_params *p) { return p->rho2 > 0.0 && p->
 // is a CU for every block.  Measured as above, FP32: 8 x 64 4.3 -> 3.5,
 // 40 x 100 5.0 -> 3.5, 128 x 128 5.0 -> 3.7 (tiles of two rows), 160 x 300
 // 5.7 -> 4.6, 224 x 200 5.6 -> 4.6 (four); FP64: 8 x 64 5.5 -> 4.0, 40 x 100
-// 5.3 -> 4.0, 200 x 100 5.9 -> 4.6, 160 x 300 6.5 -> 5.5.  With more blocks
-// than CUs they lose: 256 x 512 FP32 7.7 -> 11.7, FP64 11.5 -> 14.3.  That also
-// keeps tall grids of few columns on single steps, whose strips are mostly
+// 5.3 -> 4.0, 200 x 100 5.9 -> 4.6, 160 x 300 6.5 -> 5.5.  A tile of eight
+// rows has sixteen waves, four a SIMD with 128 registers each, and spills; it
+// loses where a step alone has at most one 64 x 4 tile a CU (742 x 75 5.8 ->
+// 6.9, 64 x 859 5.5 -> 6.7, 301 x 176 5.8 -> 6.7) and gains where that shares
+// CUs (144 x 364 6.8 -> 6.3, 1023 x 72 7.1 -> 6.9, 1367 x 53 7.2 -> 6.9).  With
+// more blocks than CUs pairs lose: 256 x 512 FP32 7.7 -> 11.7, FP64 11.5 ->
+// 14.3.  That also keeps tall grids of few columns on single steps, whose strips are mostly
 // margin: 8 x 4096 FP32 (512 tiles of eight rows) 10.4 -> 11.2, while 8 x 2048
 // (256) gains, 8.0 -> 6.3.  Up to 256 sites one block stepping alone
 // (small_step_kernel) takes them.
@@ -311,6 +323,26 @@ struct PairLaunch {
   int nparts;                       // diagnostic partials
   int tile;                         // rows of a tile where the pairs go in tiles (pair_tile_kernel)
 };
+// Blocks of nw waves that hold the strips of at most cols columns.
+inline int strip_groups(int nx, int cols, int nw) {
+  return ((nx + cols - 1) / cols + nw - 1) / nw;
+}
+// Many-wave blocks: above 3M sites, where they need at most a third more waves
+// than the width has strips (LBE_CSF_PAIR_NW forces the choice).
+inline bool wide_blocks(int nx, int cols, int nw, size_t n) {
+  if (const char *w = std::getenv("LBE_CSF_PAIR_NW")) return std::atoi(w) > 2;
+  return n > 3000000 && 3 * nw * strip_groups(nx, cols, nw) <= 4 * strip_groups(nx, cols, 1);
+}
+// Whether strips of that many waves across the width beat a step alone, which
+// goes in tiles of 64 columns up to 1.5M sites: the lines measured above.
+inline bool pairs_pay(int nx, size_t n, bool fp32, int waves) {
+  const int tiles = (nx + kTileX - 1) / kTileX;
+  if (n > 1500000) return true;
+  if (fp32) return n >= 1250000 && waves < 2 * tiles;
+  if (n >= 650000) return nx > kPairCols;
+  return (n >= 580000 && 4 * waves <= 5 * tiles) || (n >= (size_t)1 << 19 && nx % 256 == 0) ||
+         (n >= 500000 && nx >= 2048);
+}
 inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
   PairLaunch L{0, 0, 0, 0, 0, 0};
   const bool fp32 = p->precision == LBE_CSF_FP32_DEV;
@@ -326,7 +358,7 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
   const size_t n = (size_t)p->nx * p->ny;
   const char *rows = std::getenv("LBE_CSF_PAIR_ROWS");
   // Tiles of 2, 4 or (FP32) 8 rows, the fewest that still give every block a
-  // CU of its own.
+  // CU of its own; 8 only where one step's tiles outnumber the CUs.
   if (want == 2 || (!forced && n > kPairTileMin)) {
     const int strips = (p->nx + kPairCols - 1) / kPairCols;
     const int wx = (p->nx + strips - 1) / strips;
@@ -336,17 +368,16 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
     while (ty < (fp32 ? 8 : 4) && blocks(ty) > kNumCUs) ty *= 2;
     if (rows && (std::atoi(rows) == 2 || std::atoi(rows) == 4 || (fp32 && std::atoi(rows) == 8)))
       ty = std::atoi(rows);
-    if (want == 2 || blocks(ty) <= kNumCUs) {
+    const bool crowded = tile_blocks(p->nx, p->ny) > kNumCUs;
+    if (want == 2 || (blocks(ty) <= kNumCUs && (ty < 8 || crowded))) {
       L.tile = L.rows = ty;
       L.nblocks = L.nparts = (int)blocks(ty);
       return L;
     }
   }
-  if (!forced && n < (size_t)(fp32 ? 1200000 : 500000)) return L;
-  bool wide = n > 3000000;
-  if (const char *w = std::getenv("LBE_CSF_PAIR_NW")) wide = std::atoi(w) > 2;
-  L.nw = fp32 ? (wide ? 8 : 1) : 2;
-  const int ngroups = ((p->nx + kPairCols - 1) / kPairCols + L.nw - 1) / L.nw;
+  L.nw = fp32 ? (wide_blocks(p->nx, kPairCols, 8, n) ? 8 : 1) : 2;
+  const int ngroups = strip_groups(p->nx, kPairCols, L.nw);
+  if (!forced && !pairs_pay(p->nx, n, fp32, ngroups * L.nw)) return PairLaunch{};
   const int slots = kNumCUs * (fp32 ? 8 : 4) / L.nw;
   // strips fill their blocks evenly; a grid with few columns takes fewer
   const int wx = std::max(4, (p->nx + ngroups * L.nw - 1) / (ngroups * L.nw));
@@ -362,12 +393,16 @@ inline PairLaunch pair_launch(const lbe_csf_params *p, size_t state_bytes) {
 
 // Steps with two densities in one launch (density_step_kernel): strips and
 // chunks of one wave each; rows = 0 where they take two launches.  Taken from
-// 1.35M sites in FP32 and 500k in FP64.  Measured on MI355X, two launches ->
-// one, us per step, FP32: 4096^2 1218 -> 994, 2048^2 326 -> 268, 1500^2
-// 207 -> 149, below the line 1300 x 1000 94.6 -> 94.8, 1200 x 1020 81 -> 88,
-// 1030 x 777 50 -> 55; FP64: 4096^2 2226 -> 1458, 1500^2 359 -> 225, 1030 x 777
-// 112 -> 85, 512 x 1024 56 -> 48, below it 320 x 600 23.8 -> 28.6 (ten rows of
-// latency for chunks of four).  The FP32 kernel needs 290 registers, so a CU
+// 1.5M sites in FP32, where those leave the tile kernel, and 300k in FP64.
+// Measured on MI355X, two launches -> one, us per step, FP32: 4096^2 1218 ->
+// 994, 2048^2 326 -> 268, 1500^2 207 -> 149, 1024 x 1514 139 -> 112, below the
+// line 1024 x 1417 112 -> 105 but 40 x 36251 121 -> 137, 1300 x 1000 94.6 ->
+// 94.8, 1030 x 777 50 -> 55; FP64: 4096^2 2226 -> 1458, 1500^2 359 -> 225, 1030
+// x 777 112 -> 85, 512 x 1024 56 -> 48, 512 x 704 41 -> 39, 254 x 1182 35.5 ->
+// 35.7, 167 x 1797 37.5 -> 35.1, below it 512 x 469 29.8 -> 32.1, 320 x 600
+// 23.8 -> 28.6 (ten rows of latency for chunks of four).  Widths of 59 to 64
+// columns, two strips for one tile, stay with two launches: FP32 60 x 26667 166
+// -> 198, FP64 60 x 10834 74 -> 88.  The FP32 kernel needs 290 registers, so a CU
 // holds four of its waves too (held to 256 for eight it spills: 4096^2 1426).
 // Above 3M sites in FP64 neighbouring strips march in step in one block, as in
 // pair_launch: 4096^2 1777 with one wave a block, 1458 with four; the FP32 form
@@ -383,12 +418,13 @@ inline PairLaunch density_launch(const lbe_csf_params *p, size_t state_bytes) {
                         "LBE_CSF_TILE", "LBE_CSF_SMALL"})
     if (!forced && std::getenv(v)) return L;
   const size_t n = (size_t)p->nx * p->ny;
-  if (!forced && n < (size_t)(fp32 ? 1350000 : 500000)) return L;
   constexpr int cols = 64 - 2 * kDensityHalo;
-  bool wide = n > 3000000;
-  if (const char *w = std::getenv("LBE_CSF_PAIR_NW")) wide = std::atoi(w) > 2;
-  L.nw = !fp32 && wide ? 4 : 1;
-  const int ngroups = ((p->nx + cols - 1) / cols + L.nw - 1) / L.nw;
+  L.nw = !fp32 && wide_blocks(p->nx, cols, 4, n) ? 4 : 1;
+  const int ngroups = strip_groups(p->nx, cols, L.nw);
+  const int tiles = (p->nx + kTileX - 1) / kTileX;
+  if (!forced && (n < (size_t)(fp32 ? 1500000 : 300000) ||
+                  (ngroups * L.nw >= 2 * tiles && (fp32 || n <= 1500000))))
+    return L;
   const int wx = std::max(4, (p->nx + ngroups * L.nw - 1) / (ngroups * L.nw));
   L.nstrips = (p->nx + wx - 1) / wx;
   const int chunks = std::max(1, kNumCUs * 4 / L.nw / ngroups);

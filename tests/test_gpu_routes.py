@@ -64,16 +64,38 @@ def test_pair_block_override(lbe, monkeypatch, precision, nw, want):
     (16, 16, "fp64", 0, ["small_step_kernel"]),
     (8, 64, "fp64", 0, ["pair_tile_kernel"] * 2), (160, 300, "fp32_dev", 0, ["pair_tile_kernel"] * 2),
     (8, 4096, "fp32_dev", 0, ["tile_step_kernel"] * 4),
+    (742, 75, "fp32_dev", 0, ["tile_step_kernel"] * 4),
+    (144, 364, "fp32_dev", 0, ["pair_tile_kernel"] * 2),
     (256, 512, "fp32_dev", 0, ["tile_step_kernel"] * 4),
-    (720, 720, "fp64", 0, ["pair_step_kernel"] * 2),
+    (728, 728, "fp64", 0, ["tile_step_kernel"] * 4), (743, 790, "fp64", 0, ["pair_step_kernel"] * 2),
+    (512, 1030, "fp64", 0, ["pair_step_kernel"] * 2), (130, 4462, "fp64", 0, ["tile_step_kernel"] * 4),
+    (130, 5010, "fp64", 0, ["pair_step_kernel"] * 2), (23, 28696, "fp64", 0, ["tile_step_kernel"] * 4),
+    (23, 66000, "fp64", 0, ["pair_step_kernel"] * 2), (4000, 126, "fp64", 0, ["pair_step_kernel"] * 2),
     (1160, 1020, "fp32_dev", 0, ["tile_step_kernel"] * 4),
-    (1200, 1030, "fp32_dev", 0, ["pair_step_kernel"] * 2),
-    (1200, 1030, "fp32_dev", 2.0, ["tile_step_kernel"] * 8),
-    (1300, 1100, "fp32_dev", 2.0, ["density_step_kernel"] * 4),
-    (720, 720, "fp64", 2.0, ["density_step_kernel"] * 4)])
+    (1250, 1010, "fp32_dev", 0, ["pair_step_kernel"] * 2),
+    (60, 22001, "fp32_dev", 0, ["tile_step_kernel"] * 4),
+    (60, 25834, "fp32_dev", 0, ["pair_step_kernel"] * 2),
+    (1300, 1100, "fp32_dev", 2.0, ["tile_step_kernel"] * 8),
+    (1400, 1100, "fp32_dev", 2.0, ["density_step_kernel"] * 4),
+    (60, 26000, "fp32_dev", 2.0, ["step_kernel"] * 8),
+    (500, 590, "fp64", 2.0, ["tile_step_kernel"] * 8),
+    (500, 610, "fp64", 2.0, ["density_step_kernel"] * 4)])
 def test_default_routes(lbe, monkeypatch, nx, ny, precision, rho2, want):
     """Four plain steps on grids at both sides of each rule."""
     for v in ("PAIR", "PAIR_NW", "PAIR_ROWS", "NW", "ROWS", "PIPE", "STREAM", "TILE", "SMALL"):
         monkeypatch.delenv("LBE_CSF_" + v, raising=False)
     ks = kernels(lbe, nx, ny, precision, 4, **(dict(rho2=rho2) if rho2 else {}))
     assert [k[0] for k in ks] == want, ks
+
+
+@pytest.mark.parametrize("nx,ny,precision,rho2,nw", [
+    (52, 58654, "fp32_dev", 0, "1"), (254, 12008, "fp32_dev", 0, "1"), (400, 7626, "fp32_dev", 0, "8"),
+    (2000, 1526, "fp32_dev", 0, "8"), (23, 132609, "fp64", 2.0, "1"), (800, 3800, "fp64", 2.0, "4")])
+def test_blocks_of_large_grids(lbe, monkeypatch, nx, ny, precision, rho2, nw):
+    """Above 3M sites the waves of a block take neighbouring strips, on widths
+    that fill such blocks."""
+    for v in ("PAIR", "PAIR_NW", "PAIR_ROWS", "NW", "ROWS", "PIPE", "STREAM", "TILE", "SMALL"):
+        monkeypatch.delenv("LBE_CSF_" + v, raising=False)
+    ks = kernels(lbe, nx, ny, precision, 2, **(dict(rho2=rho2) if rho2 else {}))
+    want = "density_step_kernel" if rho2 else "pair_step_kernel"
+    assert all(k[0] == want and k[1][-1] == nw for k in ks) and len(ks) == (2 if rho2 else 1), ks
